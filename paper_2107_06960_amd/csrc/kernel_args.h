@@ -74,12 +74,13 @@ struct StageArgs {
 // Kernel families the runtime picks from.
 enum KernelKind {
   K_CONV_MFMA = 0,      // matrix cores, operands staged through registers (fp32)
-  K_CONV_DIRECT = 1,    // vector ALUs, any shape
+  K_CONV_DIRECT = 1,    // vector ALUs, any shape (frames past 32-bit byte offsets)
   K_POOL = 2,           // lone max-pool
   K_CONV_RGB = 3,       // 3-channel first layer, vector ALUs
   K_CONV_RGB_MFMA = 4,  // 3-channel first layer, matrix cores (bf16)
   K_CONV_RING = 5,      // matrix cores, operands streamed into an LDS ring (bf16)
-  K_CONV_PATCH = 6      // 3x3 on the matrix cores, input patch shared by the taps (bf16)
+  K_CONV_PATCH = 6,     // 3x3 on the matrix cores, input patch shared by the taps (bf16)
+  K_CONV_ANY = 7        // matrix cores, any filter, stride, padding and channels
 };
 
 // Conv outputs (rows x columns) per workgroup of the matrix-core first-layer
@@ -141,6 +142,11 @@ struct MfmaShape {
 #define MAFAT_RING_TUNE_SHAPES
 #endif
 
+// Instantiated block shapes of the any-filter kernel: (bm, bn, K groups).
+#define MAFAT_ANY_SHAPES                                                           \
+  MAFAT_ANY(32, 32, 1) MAFAT_ANY(32, 32, 2) MAFAT_ANY(32, 32, 4) MAFAT_ANY(64, 32, 1) \
+  MAFAT_ANY(32, 64, 1) MAFAT_ANY(32, 64, 2) MAFAT_ANY(64, 64, 1) MAFAT_ANY(128, 64, 2)
+
 // Launch one stage chunk.  `units_per_block` is what the kernel covers per
 // block along the pixel axis (used to fill mblk_prefix by the caller).
 // Optional kernel timestamps: `start` is recorded when the launched kernel
@@ -155,6 +161,10 @@ hipError_t launch_stage(int kind, int dtype, int f, bool pool, MfmaShape shape,
 // Launch one bf16 LDS-ring convolution stage chunk (conv_ring.hip).
 hipError_t launch_conv_ring(int f, bool pool, const MfmaShape& shape, const StageArgs& args,
                             hipStream_t stream, LaunchEvents ev);
+
+// Launch one any-filter matrix-core convolution stage chunk (conv_any.hip).
+hipError_t launch_conv_any(int dtype, bool pool, const MfmaShape& shape, const StageArgs& args, hipStream_t stream,
+                           LaunchEvents ev);
 
 // Launch one bf16 3x3 patch-kernel stage chunk (conv_patch.hip).
 hipError_t launch_conv_patch(bool pool, const MfmaShape& shape, const StageArgs& args, hipStream_t stream,

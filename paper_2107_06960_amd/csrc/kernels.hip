@@ -13,10 +13,10 @@
 //                       bf16: v_mfma_f32_16x16x32_bf16; fp32:
 //                       v_mfma_f32_16x16x4_f32.  Operand tiles are staged
 //                       global -> registers -> LDS (double buffered).
-//   conv_direct_kernel  vector-ALU direct convolution for layers whose
-//                       channel count does not fill a K chunk (the 3-channel
-//                       first layer): one thread per output pixel (or per
-//                       2x2 pool window), weights through the scalar cache.
+//   conv_direct_kernel  vector-ALU direct convolution for frames too large for
+//                       32-bit byte offsets (the other kernels' buffer
+//                       descriptors): one thread per output pixel (or per 2x2
+//                       pool window), weights through the scalar cache.
 //   conv_rgb_kernel     the 3-channel first layer on the vector ALUs
 //                       (fp32), patch in registers.
 //   conv_rgb_mfma_kernel  the 3-channel first layer in bf16 on the matrix
@@ -926,7 +926,7 @@ extern "C" int mafat_debug_trace(long long* host_out) {
 #endif
 
 int block_units(int kind, MfmaShape shape) {
-  if (kind == K_CONV_MFMA || kind == K_CONV_RING) return shape.bm;
+  if (kind == K_CONV_MFMA || kind == K_CONV_RING || kind == K_CONV_ANY) return shape.bm;
   if (kind == K_CONV_DIRECT || kind == K_CONV_RGB) return 256;
   return 64;
 }

@@ -37,9 +37,9 @@ int fail(int status, const std::string& msg) {
 // input channels), output channels in multiples of 16, and its weights
 // addressable with 32-bit byte offsets (the source buffer is checked per
 // launch).
-// The matrix-core and first-layer kernels take "same" convolutions only:
-// f = 1 or 3, stride 1, padding (f - 1) / 2.  Every other convolution (and
-// channel count) runs on the generic kernel.
+// These and the first-layer kernels take "same" convolutions only: f = 1 or
+// 3, stride 1, padding (f - 1) / 2.  Every other convolution (and channel
+// count) runs on the any-filter kernel.
 bool same_conv(const Stage& S) {
   return S.kind == STAGE_CONV && (S.f == 1 || S.f == 3) && S.s == 1 && S.p == (S.f - 1) / 2;
 }
@@ -55,6 +55,13 @@ bool mfma_ok(const Stage& S, int dtype) {
 bool rgb_ok(const Stage& S) {
   return same_conv(S) && S.cin == 3 && S.f == 3 &&
          (S.cout == 8 || S.cout == 16 || S.cout == 32 || S.cout == 64);
+}
+
+// The any-filter matrix-core kernel: any filter, stride, padding and channel
+// counts whose weights are addressable with 32-bit byte offsets.
+bool any_ok(const Stage& S, int dtype) {
+  const int64_t esz = (dtype == MAFAT_BF16) ? 2 : 4;
+  return S.kind == STAGE_CONV && static_cast<int64_t>(S.cout) * S.f * S.f * S.cin * esz < (1ll << 31);
 }
 
 // Tuning builds only: MAFAT_TUNE="first_layer:bm,bn,depth[,chan_major[,kg[,kind[,kord[,br,bc[,wgm,wgn]]]]]];..."
@@ -90,6 +97,51 @@ StageConfig tune_override(const Stage& S, StageConfig c) {
   return c;
 }
 
+// Block shape and K groups of the any-filter kernel, from a model of one
+// compute unit fitted to a sweep of eleven layers (7x7/2 to 1x1/2, both data
+// types, 18x16 to 224x200; within 15 % of most points): a workgroup costs
+// ~2 us (decode, first loads, epilogue) and, per K stage, ~0.28 us of latency
+// (wait, barrier, LDS reads, MFMA chain) plus its MFMAs and its operand
+// bytes (~130 GB/s per unit; ragged channels, fetched value by value, ~10
+// GB/s in bf16 and twice that in fp32); workgroups that share a unit hide
+// each other's latency but not each other's work.  So a small layer with a
+// long K takes small blocks and several K groups (5x5 64->64 fp32 on nine
+// 19x17 tiles: 14.4 us with 32x32 blocks and four groups, 42.9 us with 64x64
+// and one), a larger one wider blocks (3x3/2 128->256 bf16 on 76x76, four
+// frames: 11.2 us with 128x64 and two groups, 15.8 us with 32x32 and one).
+void choose_any(const Stage& S, int batch, int dtype, StageConfig* c) {
+  const int esz = (dtype == MAFAT_BF16) ? 2 : 4, epv = 16 / esz;
+  const bool gather = S.cin % epv != 0;
+  const int64_t pieces = gather ? static_cast<int64_t>(S.f) * ((S.f * S.cin + epv - 1) / epv)
+                                : static_cast<int64_t>(S.f) * S.f * (S.cin / epv);
+  const double load_rate = gather ? (dtype == MAFAT_BF16 ? 10e3 : 20e3) : 130e3;  // bytes per us and unit
+  const double mfma_rate = (dtype == MAFAT_BF16 ? 4096.0 : 256.0) * 2400.0;       // flop per us and unit
+  struct AS { int bm, bn, kg; };
+  static const AS kAny[] = {
+#define MAFAT_ANY(bm_, bn_, kg_) {bm_, bn_, kg_},
+      MAFAT_ANY_SHAPES
+#undef MAFAT_ANY
+  };
+  double best = 1e30;
+  for (const AS& r : kAny) {
+    int64_t mb = 0;
+    for (const TileGeom& T : S.tiles) mb += (static_cast<int64_t>(T.ch) * T.cw + r.bm - 1) / r.bm;
+    const int64_t blocks = mb * ((S.cout + r.bn - 1) / r.bn);
+    const double wgs = static_cast<double>(blocks) * batch;
+    const int slots = (gather ? 2 : 3) * r.kg * (r.bm + r.bn) * 128;
+    const int occ = std::max(1, std::min(160 * 1024 / slots, 8 / r.kg));
+    const double rounds = std::ceil(wgs / (256.0 * occ));
+    const double share = std::min<double>(occ, std::ceil(wgs / 256.0));  // workgroups on one unit
+    const double stages = static_cast<double>((pieces + 8 * r.kg - 1) / (8 * r.kg));
+    const double busy = r.kg * (2.0 * r.bm * r.bn * 8 * epv / mfma_rate + (r.bm + r.bn) * 128.0 / load_rate);
+    const double t = rounds * (2.0 + stages * std::max(0.28 + busy, share * busy));
+    if (t < best * 0.97) {
+      best = t;
+      c->bm = r.bm; c->bn = r.bn; c->kg = r.kg; c->blocks = blocks;
+    }
+  }
+}
+
 }  // namespace
 
 // Block tile and pipeline depth for the matrix-core kernel, from a small
@@ -103,7 +155,8 @@ StageConfig choose_config(const Stage& S, int batch, int dtype) {
   c.bm = 64; c.bn = 64; c.depth = 3; c.kg = 1; c.wgm = 2; c.wgn = 2; c.br = 0; c.bc = 0;
   if (S.kind == STAGE_POOL) { c.kind = K_POOL; return c; }
   if (!mfma_ok(S, dtype)) {
-    c.kind = rgb_ok(S) ? K_CONV_RGB : K_CONV_DIRECT;
+    c.kind = rgb_ok(S) ? K_CONV_RGB : any_ok(S, dtype) ? K_CONV_ANY : K_CONV_DIRECT;
+    if (c.kind == K_CONV_ANY) choose_any(S, batch, dtype, &c);
     // bf16 first layer with 16/32/64 outputs: K = 27 padded to one MFMA K.
     if (c.kind == K_CONV_RGB && dtype == MAFAT_BF16 && (S.cout == 16 || S.cout == 32 || S.cout == 64)) {
       c.kind = K_CONV_RGB_MFMA;
@@ -350,7 +403,7 @@ StageConfig stage_config(const mafat_plan& P, const Group& G, const Stage& S, in
   const auto& din = P.dims[G.l0];
   const int64_t src_frame = (S.src_buf == BUF_GROUP_IO) ? static_cast<int64_t>(din[0]) * din[1] * din[2]
                                                         : G.scratch_frame;
-  if ((c.kind == K_CONV_MFMA || c.kind == K_CONV_RING || c.kind == K_CONV_PATCH) &&
+  if ((c.kind == K_CONV_MFMA || c.kind == K_CONV_RING || c.kind == K_CONV_PATCH || c.kind == K_CONV_ANY) &&
       src_frame * esz >= (1ll << 31))
     c.kind = K_CONV_DIRECT;
   return c;
@@ -628,7 +681,7 @@ int run_group_impl(const mafat_plan* plan, int g, int s_begin, int s_end, int ba
       const StageConfig cfg = first ? first_pair_config(*S2, batch) : scfg;
       const Stage& SC = first ? *S2 : S;  // the convolution whose GEMM the launch computes
       const int kind = cfg.kind;
-      const bool matrix = (kind == K_CONV_MFMA || kind == K_CONV_RING || kind == K_CONV_PATCH);
+      const bool matrix = (kind == K_CONV_MFMA || kind == K_CONV_RING || kind == K_CONV_PATCH || kind == K_CONV_ANY);
       const MfmaShape shape{cfg.bm, cfg.bn, cfg.depth, cfg.kg, cfg.wgm, cfg.wgn, cfg.kord, cfg.br, cfg.bc};
       const int bu = (kind == K_CONV_RGB) ? 256 / (S.cout / 8) : block_units(kind, shape);
       StageArgs A;
@@ -752,6 +805,8 @@ int run_group_impl(const mafat_plan* plan, int g, int s_begin, int s_end, int ba
           e = launch_conv_patch_fused(A, stream, lev);
         } else if (kind == K_CONV_PATCH) {
           e = launch_conv_patch(S.pool, shape, A, stream, lev);
+        } else if (kind == K_CONV_ANY) {
+          e = launch_conv_any(dtype, S.pool, shape, A, stream, lev);
         } else {
           e = launch_stage(kind, dtype, same_conv(S) ? S.f : 0, S.pool, shape, A, stream, lev);
         }
