@@ -40,6 +40,7 @@ struct StageArgs {
   int32_t total_blocks; // batch * mblk_total * nblk_n
   int32_t chan_major;   // 1: blocks ordered channel-block-major (each XCD gets a slice of
                         //    the weights); 0: pixel-block-major (a slice of the pixels)
+  int32_t block_px;     // output pixels per workgroup (pool kernel)
   int32_t w_packed;     // patch kernel: w is packed [cout/BN][cin/32][9][BN][32] (else KRSC)
   // Fused second layer (a 1x1 convolution of this stage's output, computed
   // in the same workgroup): weights [cout2][cin = cout], its scale and bias.

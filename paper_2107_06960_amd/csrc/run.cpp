@@ -153,7 +153,19 @@ void choose_any(const Stage& S, int batch, int dtype, StageConfig* c) {
 StageConfig choose_config(const Stage& S, int batch, int dtype) {
   StageConfig c{};
   c.bm = 64; c.bn = 64; c.depth = 3; c.kg = 1; c.wgm = 2; c.wgn = 2; c.br = 0; c.bc = 0;
-  if (S.kind == STAGE_POOL) { c.kind = K_POOL; return c; }
+  if (S.kind == STAGE_POOL) {
+    // One thread per output pixel and 16-byte piece (or value, where the
+    // channels are no whole pieces), more pieces per thread only where that
+    // still leaves eight workgroups per compute unit.
+    c.kind = K_POOL;
+    const int epv = (dtype == MAFAT_BF16) ? 8 : 4;
+    const int64_t per = (S.cin % epv == 0) ? S.cin / epv : S.cin;
+    int64_t px = 0;
+    for (const TileGeom& T : S.tiles) px += static_cast<int64_t>(T.ch) * T.cw;
+    const int64_t each = std::min<int64_t>(std::max<int64_t>(px * per * batch / (256ll * 8 * 256), 1), 4);
+    c.bm = static_cast<int>(std::max<int64_t>(256 * each / per, 1));
+    return c;
+  }
   if (!mfma_ok(S, dtype)) {
     c.kind = rgb_ok(S) ? K_CONV_RGB : any_ok(S, dtype) ? K_CONV_ANY : K_CONV_DIRECT;
     if (c.kind == K_CONV_ANY) choose_any(S, batch, dtype, &c);
@@ -720,6 +732,7 @@ int run_group_impl(const mafat_plan* plan, int g, int s_begin, int s_end, int ba
       A.act = SC.act;
       A.nblk_n = matrix ? (SC.cout + shape.bn - 1) / shape.bn : 1;
       A.chan_major = matrix ? cfg.chan_major : 0;
+      A.block_px = bu;
       A.w_packed = (plan->packed_weights && kind == K_CONV_PATCH) ? 1 : 0;
       for (int t0 = b0; t0 < b1; t0 += kMaxTilesPerLaunch) {
         const int t1 = std::min(b1, t0 + kMaxTilesPerLaunch);
