@@ -111,33 +111,6 @@ __device__ __forceinline__ void pwait_stage(int rem) {
 }
 __device__ __forceinline__ void pbarrier() { asm volatile("s_barrier" ::: "memory"); }
 
-// Byte offset of 16-byte chunk q of 64-byte weight row `row` in a slot region.
-__device__ __forceinline__ int swz(int row, int q) { return row * 64 + ((q ^ ((row >> 1) & 3)) << 4); }
-
-// GEMM rows of a block are window-major: every 4 consecutive rows are one
-// 2x2 window of the block (block sizes are even), windows row by row.  With
-// a fused pool a lane's 4 accumulator rows are then one pool window.
-template <int BC>
-__device__ __forceinline__ void block_pixel(int r, int* py, int* px) {
-  constexpr int WC = BC / 2;  // windows per block row
-  const int q = r >> 2, s = r & 3, wy = q / WC;
-  *py = 2 * wy + (s >> 1);
-  *px = 2 * (q - wy * WC) + (s & 1);
-}
-
-// Swizzle key of patch pixel (py, px): 16-byte position p of the pixel's
-// 64-byte LDS row holds K chunk p ^ key.  A 16-byte LDS read is served 16
-// lanes per cycle from 64 banks, the lanes of one cycle being one half of
-// the wave with one parity of lane bits 2-4 (calibrated with the hardware's
-// bank-conflict counter); an MFMA fragment read (row l & 15, K chunk l >> 4)
-// is conflict-free when the 16 (pixel's LDS row index mod 4, chunk ^ key)
-// pairs of each such lane set differ.  With window-major GEMM rows, key = py & 3
-// bit-reversed makes every tap's fragment reads conflict-free for blocks
-// 8 or 16 pixels wide and leaves 0.75-1.3 extra cycles per 4-cycle read for
-// 10-, 12- and 18-wide ones (pixel-major rows with the best key of that form:
-// 0 for 16-wide blocks, 2.7-3.6 for the others).
-__device__ __forceinline__ int patch_key(int py) { return ((py & 1) << 1) | ((py >> 1) & 1); }
-
 // N2 > 0: a 1x1 convolution with N2 outputs of this stage's output (all BN
 // = c_out channels in the block) follows in the same workgroup: the block's
 // activated bf16 outputs stay in LDS and are the A operand of a second GEMM

@@ -86,19 +86,29 @@ struct BlockPos {
 struct NoEarly {
   __device__ void operator()(int) const {}
 };
-template <typename Early = NoEarly>
-__device__ __forceinline__ BlockPos decode_block(const StageArgs& a, KTile* tile, Early early = Early{}) {
+// One lane's entry of the per-tile tables.
+struct TileTable {
+  int pre;
+  uint32_t w[7];
+};
+__device__ __forceinline__ TileTable load_tile_table() {
   static_assert(kMaxTilesPerLaunch == 64 && sizeof(KTile) == 28, "one tile per lane of a wave");
   const int lane = static_cast<int>(threadIdx.x) & 63;
   // (C-style cast: converts from the constant address space.)
   const StageArgs* ka = (const StageArgs*)__builtin_amdgcn_kernarg_segment_ptr();
-  const int pre = ka->mblk_prefix[lane];
+  TileTable t;
+  t.pre = ka->mblk_prefix[lane];
   const uint32_t* tw = reinterpret_cast<const uint32_t*>(&ka->tiles[lane]);
-  uint32_t w[7];
 #pragma unroll
-  for (int k = 0; k < 7; ++k) w[k] = tw[k];
-
-  int bid = xcd_remap(static_cast<int>(blockIdx.x), a.total_blocks);
+  for (int k = 0; k < 7; ++k) t.w[k] = tw[k];
+  return t;
+}
+// Workgroup number `bid` of the launch's total_blocks.
+template <typename Early = NoEarly>
+__device__ __forceinline__ BlockPos locate_block(const StageArgs& a, const TileTable& tab, int workgroup, KTile* tile,
+                                                 Early early = Early{}) {
+  const int lane = static_cast<int>(threadIdx.x) & 63;
+  const int bid = xcd_remap(workgroup, a.total_blocks);
   const int per_frame = a.mblk_total * a.nblk_n;
   BlockPos p;
   p.frame = bid / per_frame;
@@ -114,14 +124,20 @@ __device__ __forceinline__ BlockPos decode_block(const StageArgs& a, KTile* tile
   }
   early(p.nb);
   // Tiles whose first block is at or before mg, not counting tile 0.
-  const int t = __popcll(__builtin_amdgcn_ballot_w64(lane >= 1 && lane < a.ntiles && pre <= mg));
+  const int t = __popcll(__builtin_amdgcn_ballot_w64(lane >= 1 && lane < a.ntiles && tab.pre <= mg));
   p.tile = t;
-  p.mb = mg - __builtin_amdgcn_readlane(pre, t);
+  p.mb = mg - __builtin_amdgcn_readlane(tab.pre, t);
   uint32_t tw_t[7];
 #pragma unroll
-  for (int k = 0; k < 7; ++k) tw_t[k] = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(w[k]), t));
+  for (int k = 0; k < 7; ++k)
+    tw_t[k] = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(tab.w[k]), t));
   __builtin_memcpy(tile, tw_t, sizeof(KTile));
   return p;
+}
+template <typename Early = NoEarly>
+__device__ __forceinline__ BlockPos decode_block(const StageArgs& a, KTile* tile, Early early = Early{}) {
+  const TileTable tab = load_tile_table();
+  return locate_block(a, tab, static_cast<int>(blockIdx.x), tile, early);
 }
 
 // Row reuse take-over copies carried by a launch (StageArgs::copy_*): a
@@ -153,6 +169,34 @@ __device__ __forceinline__ void carried_copies() {
     *reinterpret_cast<u32x4*>(fb + ka->copy_dst[k] + (r << 4)) = v;
   }
 }
+
+// Helpers of the patch kernels (conv_patch.hip, conv_split.hip).
+// Byte offset of 16-byte chunk q of 64-byte weight row `row` in a slot region.
+__device__ __forceinline__ int swz(int row, int q) { return row * 64 + ((q ^ ((row >> 1) & 3)) << 4); }
+
+// GEMM rows of a block are window-major: every 4 consecutive rows are one
+// 2x2 window of the block (block sizes are even), windows row by row.  With
+// a fused pool a lane's 4 accumulator rows are then one pool window.
+template <int BC>
+__device__ __forceinline__ void block_pixel(int r, int* py, int* px) {
+  constexpr int WC = BC / 2;  // windows per block row
+  const int q = r >> 2, s = r & 3, wy = q / WC;
+  *py = 2 * wy + (s >> 1);
+  *px = 2 * (q - wy * WC) + (s & 1);
+}
+
+// Swizzle key of patch pixel (py, px): 16-byte position p of the pixel's
+// 64-byte LDS row holds K chunk p ^ key.  A 16-byte LDS read is served 16
+// lanes per cycle from 64 banks, the lanes of one cycle being one half of
+// the wave with one parity of lane bits 2-4 (calibrated with the hardware's
+// bank-conflict counter); an MFMA fragment read (row l & 15, K chunk l >> 4)
+// is conflict-free when the 16 (pixel's LDS row index mod 4, chunk ^ key)
+// pairs of each such lane set differ.  With window-major GEMM rows, key = py & 3
+// bit-reversed makes every tap's fragment reads conflict-free for blocks
+// 8 or 16 pixels wide and leaves 0.75-1.3 extra cycles per 4-cycle read for
+// 10-, 12- and 18-wide ones (pixel-major rows with the best key of that form:
+// 0 for 16-wide blocks, 2.7-3.6 for the others).
+__device__ __forceinline__ int patch_key(int py) { return ((py & 1) << 1) | ((py >> 1) & 1); }
 
 // Output pixel of row m of a tile's GEMM.  Without a fused pool the rows run
 // over the computed rectangle in row-major order; with one, every 4

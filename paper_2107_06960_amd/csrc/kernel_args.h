@@ -81,7 +81,8 @@ enum KernelKind {
   K_CONV_RGB_MFMA = 4,  // 3-channel first layer, matrix cores (bf16)
   K_CONV_RING = 5,      // matrix cores, operands streamed into an LDS ring (bf16)
   K_CONV_PATCH = 6,     // 3x3 on the matrix cores, input patch shared by the taps (bf16)
-  K_CONV_ANY = 7        // matrix cores, any filter, stride, padding and channels
+  K_CONV_ANY = 7,       // matrix cores, any filter, stride, padding and channels
+  K_CONV_SPLIT = 8      // float32 3x3 on the bf16 matrix cores, operands in three parts
 };
 
 // Conv outputs (rows x columns) per workgroup of the matrix-core first-layer
@@ -143,6 +144,14 @@ struct MfmaShape {
 #define MAFAT_RING_TUNE_SHAPES
 #endif
 
+// Instantiated split kernel shapes: (br, bc, bm, bn, wgm, wgn).
+#define MAFAT_SPLIT_SHAPES           \
+  MAFAT_SPLIT(8, 16, 128, 64, 4, 2)  \
+  MAFAT_SPLIT(8, 16, 128, 32, 4, 2)  \
+  MAFAT_SPLIT(10, 10, 128, 32, 4, 2) \
+  MAFAT_SPLIT(8, 8, 64, 64, 4, 2)    \
+  MAFAT_SPLIT(8, 8, 64, 32, 2, 2)
+
 // Instantiated block shapes of the any-filter kernel: (bm, bn, K groups).
 #define MAFAT_ANY_SHAPES                                                           \
   MAFAT_ANY(32, 32, 1) MAFAT_ANY(32, 32, 2) MAFAT_ANY(32, 32, 4) MAFAT_ANY(64, 32, 1) \
@@ -162,6 +171,10 @@ hipError_t launch_stage(int kind, int dtype, int f, bool pool, MfmaShape shape,
 // Launch one bf16 LDS-ring convolution stage chunk (conv_ring.hip).
 hipError_t launch_conv_ring(int f, bool pool, const MfmaShape& shape, const StageArgs& args,
                             hipStream_t stream, LaunchEvents ev);
+
+// Launch one float32 3x3 split-operand stage chunk (conv_split.hip).
+hipError_t launch_conv_split(bool pool, const MfmaShape& shape, const StageArgs& args, hipStream_t stream,
+                             LaunchEvents ev);
 
 // Launch one any-filter matrix-core convolution stage chunk (conv_any.hip).
 hipError_t launch_conv_any(int dtype, bool pool, const MfmaShape& shape, const StageArgs& args, hipStream_t stream,

@@ -142,6 +142,44 @@ void choose_any(const Stage& S, int batch, int dtype, StageConfig* c) {
   }
 }
 
+// Block shape of the float32 3x3 split kernel: a launch takes rounds of one
+// workgroup per compute unit (two for the smallest shape's LDS), a round one
+// step per chunk and filter row plus ~2.4 us (decode, first loads, epilogue).
+// Step times from a sweep of fifteen layers (YOLOv2's at 416x416 on 3x3 tiles,
+// a VGG-style stack, 64 and 256 channels at larger batches; launch times
+// within 15 %): a step costs the larger block little more than the smaller
+// one (its MFMAs cover more of the split's vector work), so blocks shrink only
+// to fill the units.  Against the fp32 MFMA kernel, which took these layers
+// before: 3x3 128->256 on 76x76, four frames 160.6 -> 90.6 us; 208x208 32->64
+// on nine tiles 51.1 -> 35.0 us; 26x26 256->512 47.1 -> 32.3 us; 20x17 64->96
+// 11.7 -> 9.8 us.
+void choose_split(const Stage& S, int batch, StageConfig* c) {
+  struct SS { int br, bc, bm, bn, wgm, wgn; };
+  static const SS kSplit[] = {
+#define MAFAT_SPLIT(br_, bc_, bm_, bn_, wgm_, wgn_) {br_, bc_, bm_, bn_, wgm_, wgn_},
+      MAFAT_SPLIT_SHAPES
+#undef MAFAT_SPLIT
+  };
+  double best = 1e30;
+  for (const SS& r : kSplit) {
+    int64_t mb = 0;
+    for (const TileGeom& T : S.tiles)
+      mb += static_cast<int64_t>((T.ch + r.br - 1) / r.br) * ((T.cw + r.bc - 1) / r.bc);
+    const int64_t blocks = mb * ((S.cout + r.bn - 1) / r.bn);
+    const double wgs = static_cast<double>(blocks) * batch;
+    const bool two = r.bm == 64 && r.bn == 32;
+    const double step = r.bm * r.bn == 128 * 64 ? (wgs > 256 ? 1.55 : 1.4)
+                        : r.bm == 128           ? (r.br == 10 ? 1.16 : 1.13)
+                        : two                   ? (wgs > 256 ? 1.17 : 0.9)
+                                                : 1.06;
+    const double t = std::ceil(wgs / (two ? 512.0 : 256.0)) * (2.4 + (S.cin / 32) * 3 * step);
+    if (t < best * 0.99) {
+      best = t;
+      c->br = r.br; c->bc = r.bc; c->bm = r.bm; c->bn = r.bn; c->wgm = r.wgm; c->wgn = r.wgn; c->blocks = blocks;
+    }
+  }
+}
+
 }  // namespace
 
 // Block tile and pipeline depth for the matrix-core kernel, from a small
@@ -247,6 +285,9 @@ StageConfig choose_config(const Stage& S, int batch, int dtype) {
     int64_t mb = 0;
     for (const TileGeom& T : S.tiles) mb += (static_cast<int64_t>(T.ch) * T.cw + c.bm - 1) / c.bm;
     c.blocks = mb * ((S.cout + c.bn - 1) / c.bn);
+  } else if (dtype != MAFAT_BF16 && S.f == 3 && S.cin % 32 == 0) {
+    c.kind = K_CONV_SPLIT;
+    choose_split(S, batch, &c);
   } else if (dtype != MAFAT_BF16) {
     c.kind = K_CONV_MFMA;
     const double clk = 2.4e9, mfma_rate = 4096.0 * clk, l2_rate = 64.0 * clk, t0 = 2e-6;
@@ -415,7 +456,8 @@ StageConfig stage_config(const mafat_plan& P, const Group& G, const Stage& S, in
   const auto& din = P.dims[G.l0];
   const int64_t src_frame = (S.src_buf == BUF_GROUP_IO) ? static_cast<int64_t>(din[0]) * din[1] * din[2]
                                                         : G.scratch_frame;
-  if ((c.kind == K_CONV_MFMA || c.kind == K_CONV_RING || c.kind == K_CONV_PATCH || c.kind == K_CONV_ANY) &&
+  if ((c.kind == K_CONV_MFMA || c.kind == K_CONV_RING || c.kind == K_CONV_PATCH || c.kind == K_CONV_ANY ||
+       c.kind == K_CONV_SPLIT) &&
       src_frame * esz >= (1ll << 31))
     c.kind = K_CONV_DIRECT;
   return c;
@@ -693,7 +735,8 @@ int run_group_impl(const mafat_plan* plan, int g, int s_begin, int s_end, int ba
       const StageConfig cfg = first ? first_pair_config(*S2, batch) : scfg;
       const Stage& SC = first ? *S2 : S;  // the convolution whose GEMM the launch computes
       const int kind = cfg.kind;
-      const bool matrix = (kind == K_CONV_MFMA || kind == K_CONV_RING || kind == K_CONV_PATCH || kind == K_CONV_ANY);
+      const bool matrix = (kind == K_CONV_MFMA || kind == K_CONV_RING || kind == K_CONV_PATCH || kind == K_CONV_ANY ||
+                          kind == K_CONV_SPLIT);
       const MfmaShape shape{cfg.bm, cfg.bn, cfg.depth, cfg.kg, cfg.wgm, cfg.wgn, cfg.kord, cfg.br, cfg.bc};
       const int bu = (kind == K_CONV_RGB) ? 256 / (S.cout / 8) : block_units(kind, shape);
       StageArgs A;
@@ -767,7 +810,7 @@ int run_group_impl(const mafat_plan* plan, int g, int s_begin, int s_end, int ba
           if (kind == K_CONV_RGB_MFMA)  // 2-D blocks of conv outputs
             total += static_cast<int64_t>((TC.ch + kRgbBlockRows - 1) / kRgbBlockRows) *
                      ((TC.cw + kRgbBlockCols - 1) / kRgbBlockCols);
-          else if (kind == K_CONV_PATCH)
+          else if (kind == K_CONV_PATCH || kind == K_CONV_SPLIT)
             total += static_cast<int64_t>((TC.ch + shape.br - 1) / shape.br) * ((TC.cw + shape.bc - 1) / shape.bc);
           else
             total += (units + bu - 1) / bu;
@@ -818,6 +861,8 @@ int run_group_impl(const mafat_plan* plan, int g, int s_begin, int s_end, int ba
           e = launch_conv_patch_fused(A, stream, lev);
         } else if (kind == K_CONV_PATCH) {
           e = launch_conv_patch(S.pool, shape, A, stream, lev);
+        } else if (kind == K_CONV_SPLIT) {
+          e = launch_conv_split(S.pool, shape, A, stream, lev);
         } else if (kind == K_CONV_ANY) {
           e = launch_conv_any(dtype, S.pool, shape, A, stream, lev);
         } else {
@@ -989,6 +1034,7 @@ extern "C" int mafat_plan_stage_kernel(const mafat_plan* plan, int32_t group, in
     switch (c.kind) {
       case K_CONV_PATCH: *kernel = MAFAT_KERNEL_PATCH; break;
       case K_CONV_RING: *kernel = MAFAT_KERNEL_RING; break;
+      case K_CONV_SPLIT:
       case K_CONV_MFMA: *kernel = MAFAT_KERNEL_MFMA_F32; break;
       case K_CONV_RGB:
       case K_CONV_RGB_MFMA: *kernel = MAFAT_KERNEL_FIRST_LAYER; break;

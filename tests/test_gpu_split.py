@@ -1,0 +1,102 @@
+"""GPU: the float32 3x3 convolution on split operands (conv_split.hip).
+
+Finite data against the oracle: blocks that are cut off on every side, output
+channels that fill no block, one and several chunks, the fused pool, batches
+and every execution of a plan.  The tolerance is that of plain float32: sums of
+K products of which each is off by at most 2^-24 and rounded at most K times,
+so max|gpu - oracle| <= 4 sqrt(K) 2^-24 max|sum| for independent roundings.
+
+Data the split cannot carry (infinities, NaN, sums past the largest float,
+operands whose parts fall below the smallest bf16) against the same sums in
+float64 on the CPU: the kernel computes such blocks again in plain float32."""
+import numpy as np
+import pytest
+
+from paper_2107_06960_amd import workloads as W
+
+from gpu_util import normwise_err, require_gpu, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+# (c_in, c_out, h, w, pool, tiling, batch)
+CASES = [(32, 64, 8, 16, False, "1x1", 1), (32, 16, 17, 9, False, "1x1", 2), (64, 80, 33, 35, True, "2x2", 1),
+         (96, 32, 20, 21, True, "1x3", 2), (256, 128, 26, 26, False, "3x3", 1), (32, 48, 130, 150, True, "2x3", 2),
+         (512, 32, 6, 5, False, "1x1", 1), (128, 256, 76, 70, False, "1x1", 2)]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "-".join(str(v) for v in c))
+def test_split_conv(orc, case):
+    require_gpu()
+    from paper_2107_06960_amd import mafat as M
+    cin, cout, h, w, pool, tiling, batch = case
+    print(f"[split] {case}", flush=True)
+    layers = [W.conv(cout)] + ([W.maxpool()] if pool else [])
+    par = W.make_inputs(layers, h, w, cin, batch, 11, "f32")
+    par["x"] = (par["x"] * 2 - 1).astype(np.float32)
+    ref = orc.forward_layers(layers, h, w, cin, par["x"], par)
+    assert M.Plan(layers, (h, w, cin), tiling).stage_kernel(0, 0, batch, "f32") == "mfma_f32"
+    for kw in ({}, {"part": True}, {"reuse": True}):
+        out = run_gpu(layers, h, w, cin, par, tiling, batch, "f32", want_cuts=False, **kw)
+        assert normwise_err(out, ref) <= 4 * np.sqrt(9 * cin) * 2.0 ** -24, kw
+
+
+def _conv64(x, par, pool):
+    """conv + scale, bias, leaky (+ pool) with the arithmetic of IEEE in float64 (CPU)."""
+    import torch
+    w = torch.from_numpy(par["w"][0]).double().permute(0, 3, 1, 2)
+    v = torch.nn.functional.conv2d(torch.from_numpy(x).double().permute(0, 3, 1, 2), w, padding=1)
+    v = v * torch.from_numpy(par["scale"][0]).double()[None, :, None, None]
+    v = v + torch.from_numpy(par["bias"][0]).double()[None, :, None, None]
+    v = torch.maximum(v, 0.1 * v)
+    if pool:
+        v = torch.nn.functional.max_pool2d(v, 2)
+    return v.permute(0, 2, 3, 1).numpy()
+
+
+@pytest.mark.parametrize("pool", [False, True])
+@pytest.mark.parametrize("kind", ["inf", "nan", "huge", "tiny", "one tiny block", "zero"])
+def test_split_special(kind, pool):
+    require_gpu()
+    print(f"[split special] {kind} pool={pool}", flush=True)
+    h, w, cin, cout = 24, 40, 64, 48
+    layers = [W.conv(cout)] + ([W.maxpool()] if pool else [])
+    par = W.make_inputs(layers, h, w, cin, 1, 5, "f32")
+    par["w"][0] = W.bf16_round(par["w"][0])  # whole in the first part: its others are zero
+    par["bias"][0][:] = 0.0
+    x = par["x"]
+    if kind == "inf":
+        x[0, 5, 7, 3] = np.inf
+    elif kind == "nan":
+        x[0, 20, 30, 1] = np.float32(np.nan)
+    elif kind == "huge":
+        x[0, 3:6] = 3e38  # sums overflow
+    elif kind == "tiny":
+        x *= np.float32(2.0 ** -118)
+    elif kind == "one tiny block":
+        x[0, :12, :20] *= np.float32(2.0 ** -118)
+    else:
+        x[:] = 0.0
+    out = run_gpu(layers, h, w, cin, par, "1x1", 1, "f32", want_cuts=False)
+    ref = _conv64(x, par, pool)
+    with np.errstate(over="ignore"):
+        ref = ref.astype(np.float32).astype(np.float64)  # past the largest float: infinite
+    if kind in ("inf", "huge", "nan"):
+        if kind == "nan":  # a pool window drops a NaN beside a number: only where the whole window is NaN
+            far = np.ones(ref.shape, bool)
+            s = 2 if pool else 1
+            far[0, 19 // s:22 // s + 1, 29 // s:32 // s + 1] = False
+            if not pool:
+                assert np.array_equal(np.isnan(out), np.isnan(ref))
+        elif kind == "huge":  # the rows that read no huge value; what an overflowing sum leaves is not fixed
+            far = np.zeros(ref.shape, bool)
+            far[0, 8 // (2 if pool else 1):] = True
+        else:
+            far = np.isfinite(ref)
+            assert np.array_equal(out[~far & ~np.isnan(ref)], ref[~far & ~np.isnan(ref)])
+        assert np.isfinite(out[far]).all() and far.mean() > 0.5
+        assert np.max(np.abs(out[far] - ref[far]) / np.max(np.abs(ref[far]))) <= 4 * np.sqrt(9 * cin) * 2.0 ** -24
+    else:
+        # every output to the precision of float32 against the block's own scale
+        for part in (np.s_[0, : 8 // (2 if pool else 1), : 16 // (2 if pool else 1)], np.s_[0]):
+            m = np.max(np.abs(ref[part]))
+            assert np.max(np.abs(out[part] - ref[part])) <= 4 * np.sqrt(9 * cin) * 2.0 ** -24 * m + 2.0 ** -148
