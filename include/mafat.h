@@ -133,9 +133,9 @@ enum {
    * to the run functions is that layer's weights repacked by
    * mafat_pack_weights: per block of output channels and 32-channel chunk,
    * the nine taps' rows one contiguous run, so the kernel's weight loads
-   * read whole cache lines.  The other layers keep KRSC.  Every batch runs
-   * the stage configurations chosen for one frame (the packing follows
-   * their output-channel blocks).  A layout of this library, not of the
+   * read whole cache lines.  The other layers keep KRSC.  The layout
+   * depends on the layers, the grid and the flags only, not on the batch
+   * or the tile batch it runs with.  A layout of this library, not of the
    * paper. */
   MAFAT_PLAN_PACKED_WEIGHTS = 2,
   /* Row reuse: the data reuse of section 3 (a tile takes the overlap that

@@ -221,14 +221,15 @@ void conv_patch_kernel(const StageArgs a) {
   const int lrow = lane >> 2, lpos = lane & 3;
   const int cin = a.cin, cout = a.cout;
   const int K = 9 * cin;
-  // Weights: KRSC, or packed per channel block and chunk ([cout/BN][cin/32]
-  // [9][BN][32], rows past c_out zero), where a chunk's BN x 9 rows are one
-  // contiguous run (whole lines for the 16-row load instructions).
+  // Weights: KRSC, or packed per block of pbn channels and chunk ([cout/pbn]
+  // [cin/32][9][pbn][32], rows past c_out zero), where a chunk's rows of one
+  // tap are contiguous runs (whole lines for the 16-row load instructions);
+  // the packing's block need not be this launch's BN.
   const int nchunk = cin >> 5;
-  const bool wpk = a.w_packed != 0;
+  const int pbn = a.block, psh = 31 - __builtin_clz(pbn | 1);  // the packing's block, a power of two
   const __amdgpu_buffer_rsrc_t rsb =
-      make_rsrc(a.w, static_cast<unsigned>(wpk ? a.nblk_n * nchunk * 9 * BN * 64 : cout * K * 2));
-  const unsigned bstride = wpk ? static_cast<unsigned>(9 * BN * 64) : 64u;  // bytes from one chunk to the next
+      make_rsrc(a.w, static_cast<unsigned>(pbn ? ((cout + pbn - 1) >> psh) * nchunk * 9 * pbn * 64 : cout * K * 2));
+  const unsigned bstride = pbn ? static_cast<unsigned>(9 * pbn * 64) : 64u;  // bytes from one chunk to the next
   // Weight loads: instruction g of a chunk's weight part fills weight rows
   // [16 g, 16 g + 16) of the slot (row = tap * BN + n); g past NB fills the
   // sink.  Chunk c adds 64 c bytes.
@@ -248,18 +249,34 @@ void conv_patch_kernel(const StageArgs a) {
   // issued while the tile table is still on its way.
   auto early = [&](int nb) {
     const int n0e = nb * BN;
+    // One loop per layout, each with as few instructions as it needs: nothing
+    // else of the launch can start before these loads.
+    auto rows = [&](auto offset) {
 #pragma unroll
-    for (int k = 0; k < NBW; ++k) {
-      const int g = k * NWAVE + wave;
-      const int row = 16 * g + lrow;           // weight row within the slot
-      const int t = row / BN, n = row - t * BN;
-      const int co = n0e + n;
-      const int chunk = lpos ^ ((row >> 1) & 3);
-      if (wpk)
-        b_off[k] = (g < NB) ? static_cast<unsigned>(((nb * nchunk) * 9 * BN + row) * 64 + chunk * 16) : 0x80000000u;
+      for (int k = 0; k < NBW; ++k) {
+        const int g = k * NWAVE + wave;
+        const int row = 16 * g + lrow;           // weight row within the slot
+        const int t = row / BN, n = row - t * BN;
+        const int chunk = lpos ^ ((row >> 1) & 3);
+        b_off[k] = (g < NB) ? offset(row, t, n) + static_cast<unsigned>(chunk * 16) : 0x80000000u;
+      }
+    };
+    if (pbn == 0) {
+      rows([&](int, int t, int n) {
+        const int co = n0e + n;
+        return co < cout ? static_cast<unsigned>((co * K + t * cin) * 2) : 0x80000000u;
+      });
+    } else {
+      // the block's first row; one packing block holds all its rows when pbn >= BN
+      const int first = (n0e >> psh) * nchunk * 9 * pbn + (n0e & (pbn - 1));
+      if (pbn == BN)
+        rows([&](int row, int, int) { return static_cast<unsigned>((first + row) * 64); });
+      else if (pbn > BN)
+        rows([&](int, int t, int n) { return static_cast<unsigned>((first + t * pbn + n) * 64); });
       else
-        b_off[k] = (g < NB && co < cout) ? static_cast<unsigned>((co * K + t * cin) * 2 + chunk * 16)
-                                         : 0x80000000u;
+        rows([&](int, int t, int n) {
+          return static_cast<unsigned>((first + ((n >> psh) * nchunk * 9 + t) * pbn + (n & (pbn - 1))) * 64);
+        });
     }
     if constexpr (PRE) {  // taps 0-4 only (their rows: instructions g < G5)
 #pragma unroll
@@ -801,7 +818,7 @@ void conv_patch_kernel(const StageArgs a) {
 template <bool POOL>
 hipError_t launch_patch_p(const MfmaShape& sh, const StageArgs& args, hipStream_t stream, LaunchEvents ev) {
   const dim3 grid(static_cast<unsigned>(args.total_blocks), args.copy_blocks > 0 ? 2u : 1u);
-#define MAFAT_PATCH(br_, bc_, bm_, bn_, wgm_, wgn_, ns_)                                               \
+#define MAFAT_PATCH(br_, bc_, bm_, bn_, wgm_, wgn_, ns_, ...)                                          \
   if (sh.br == (br_) && sh.bc == (bc_) && sh.bm == (bm_) && sh.bn == (bn_) && sh.wgm == (wgm_) &&      \
       sh.wgn == (wgn_) && sh.depth == (ns_)) {                                                        \
     if constexpr (!POOL || ((br_) % 2 == 0 && (bc_) % 2 == 0)) {                                      \
@@ -812,6 +829,7 @@ hipError_t launch_patch_p(const MfmaShape& sh, const StageArgs& args, hipStream_
     return hipErrorInvalidValue;                                                                      \
   }
   MAFAT_PATCH_SHAPES
+  MAFAT_PATCH_PAIR_SHAPES
   MAFAT_PATCH_TUNE_SHAPES
 #undef MAFAT_PATCH
   return hipErrorInvalidValue;
@@ -819,17 +837,19 @@ hipError_t launch_patch_p(const MfmaShape& sh, const StageArgs& args, hipStream_
 
 }  // namespace
 
-hipError_t launch_conv_patch_fused(const StageArgs& args, hipStream_t stream, LaunchEvents ev) {
+hipError_t launch_conv_patch_fused(const MfmaShape& sh, const StageArgs& args, hipStream_t stream, LaunchEvents ev) {
   if (args.total_blocks <= 0) return hipSuccess;
-  if (args.cout != 128 || (args.cout2 != 64 && args.cout2 != 32)) return hipErrorInvalidValue;
+  if (args.cout != 128) return hipErrorInvalidValue;
   const dim3 grid(static_cast<unsigned>(args.total_blocks), args.copy_blocks > 0 ? 2u : 1u);
-  if (args.cout2 == 64)
-    hipExtLaunchKernelGGL((conv_patch_kernel<8, 16, 128, 128, 4, 2, 1, false, 64>), grid, dim3(512), 0, stream,
-                          ev.start, ev.stop, 0, args);
-  else
-    hipExtLaunchKernelGGL((conv_patch_kernel<8, 16, 128, 128, 4, 2, 1, false, 32>), grid, dim3(512), 0, stream,
-                          ev.start, ev.stop, 0, args);
-  return hipGetLastError();
+#define MAFAT_FUSED(bc_, bm_, n2_)                                                                          \
+  if (sh.br == 8 && sh.bc == (bc_) && sh.bm == (bm_) && sh.bn == 128 && args.cout2 == (n2_)) {              \
+    hipExtLaunchKernelGGL((conv_patch_kernel<8, bc_, bm_, 128, 4, 2, 1, false, n2_>), grid, dim3(512), 0,   \
+                          stream, ev.start, ev.stop, 0, args);                                              \
+    return hipGetLastError();                                                                               \
+  }
+  MAFAT_FUSED(16, 128, 64) MAFAT_FUSED(16, 128, 32) MAFAT_FUSED(8, 64, 64) MAFAT_FUSED(8, 64, 32)
+#undef MAFAT_FUSED
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_conv_patch_first(const MfmaShape& sh, const StageArgs& args, hipStream_t stream, LaunchEvents ev) {

@@ -40,8 +40,8 @@ struct StageArgs {
   int32_t total_blocks; // batch * mblk_total * nblk_n
   int32_t chan_major;   // 1: blocks ordered channel-block-major (each XCD gets a slice of
                         //    the weights); 0: pixel-block-major (a slice of the pixels)
-  int32_t block_px;     // output pixels per workgroup (pool kernel)
-  int32_t w_packed;     // patch kernel: w is packed [cout/BN][cin/32][9][BN][32] (else KRSC)
+  int32_t block;        // patch kernel: w is packed [cout/P][cin/32][9][P][32] with this P (0: KRSC);
+                        // pool kernel: output pixels per workgroup
   // Fused second layer (a 1x1 convolution of this stage's output, computed
   // in the same workgroup): weights [cout2][cin = cout], its scale and bias.
   const void* w2;
@@ -102,26 +102,33 @@ struct MfmaShape {
   int br, bc;  // patch kernel: block of br x bc conv outputs (bm >= br * bc GEMM rows)
 };
 
-// Instantiated patch kernel shapes: (br, bc, bm, bn, wgm, wgn, ring slots).
-#define MAFAT_PATCH_SHAPES                \
-  MAFAT_PATCH(16, 16, 256, 64, 8, 1, 2)   \
-  MAFAT_PATCH(12, 12, 192, 64, 4, 2, 2)   \
-  MAFAT_PATCH(12, 16, 192, 64, 4, 2, 2)   \
-  MAFAT_PATCH(16, 12, 192, 64, 4, 2, 2)   \
-  MAFAT_PATCH(10, 10, 128, 32, 4, 1, 2)   \
-  MAFAT_PATCH(8, 8, 64, 32, 4, 2, 2)      \
-  MAFAT_PATCH(8, 16, 128, 64, 8, 1, 1)    \
+// Instantiated patch kernel shapes: (br, bc, bm, bn, wgm, wgn, ring slots),
+// then what the block chooser knows of them: workgroups that share a compute
+// unit, and the model's three times in us (choose_patch in run.cpp).
+#define MAFAT_PATCH_SHAPES                                     \
+  MAFAT_PATCH(4, 8, 32, 32, 2, 2, 2, 3, 1.90, 0.340, 0.335)    \
+  MAFAT_PATCH(8, 8, 64, 32, 2, 2, 2, 3, 2.07, 0.422, 0.398)    \
+  MAFAT_PATCH(8, 16, 128, 32, 4, 1, 1, 5, 1.80, 0.800, 0.551)  \
+  MAFAT_PATCH(8, 16, 128, 32, 4, 1, 2, 2, 2.11, 0.627, 0.546)  \
+  MAFAT_PATCH(10, 10, 128, 32, 4, 1, 2, 2, 2.32, 0.618, 0.577) \
+  MAFAT_PATCH(8, 16, 128, 64, 4, 1, 1, 3, 1.66, 1.313, 1.019)  \
+  MAFAT_PATCH(10, 10, 128, 64, 4, 1, 1, 3, 1.81, 1.282, 1.039) \
+  MAFAT_PATCH(12, 16, 192, 64, 4, 1, 1, 3, 2.30, 1.561, 1.308) \
+  MAFAT_PATCH(12, 16, 192, 64, 4, 2, 2, 1, 2.47, 1.223, 0.388) \
+  MAFAT_PATCH(16, 16, 256, 64, 8, 1, 2, 1, 2.58, 1.560, 0.040) \
+  MAFAT_PATCH(16, 16, 256, 64, 8, 1, 1, 2, 1.76, 2.100, 2.040)
+// Shapes of the fused pairs' kernels, for the pair's 3x3 stage run alone.
+#define MAFAT_PATCH_PAIR_SHAPES           \
   MAFAT_PATCH(12, 16, 192, 64, 4, 2, 1)   \
   MAFAT_PATCH(14, 18, 256, 64, 4, 2, 1)   \
-  MAFAT_PATCH(8, 16, 128, 128, 4, 2, 1)
+  MAFAT_PATCH(8, 16, 128, 64, 4, 2, 1)    \
+  MAFAT_PATCH(8, 8, 64, 64, 4, 2, 1)      \
+  MAFAT_PATCH(8, 16, 128, 128, 4, 2, 1)   \
+  MAFAT_PATCH(8, 8, 64, 128, 4, 2, 1)
 #ifdef MAFAT_TUNING
 #define MAFAT_PATCH_TUNE_SHAPES           \
-  MAFAT_PATCH(10, 10, 128, 32, 4, 1, 3)   \
-  MAFAT_PATCH(10, 10, 128, 32, 4, 1, 4)   \
-  MAFAT_PATCH(16, 12, 192, 64, 4, 2, 1)   \
-  MAFAT_PATCH(16, 16, 256, 64, 8, 1, 1)   \
-  MAFAT_PATCH(8, 16, 128, 64, 4, 1, 1)    \
-  MAFAT_PATCH(8, 16, 128, 64, 2, 2, 1)
+  MAFAT_PATCH(16, 16, 256, 64, 4, 1, 1)   \
+  MAFAT_PATCH(8, 8, 64, 32, 4, 2, 2)
 #else
 #define MAFAT_PATCH_TUNE_SHAPES
 #endif
@@ -188,7 +195,7 @@ hipError_t launch_conv_patch(bool pool, const MfmaShape& shape, const StageArgs&
 // stage (64 outputs) that follows it (conv_patch.hip): 8x16 blocks of all
 // 128 channels; args.w2 / scale2 / bias2 / cout2 / act2 describe the 1x1
 // layer, the destination fields the 1x1 stage's output.
-hipError_t launch_conv_patch_fused(const StageArgs& args, hipStream_t stream, LaunchEvents ev);
+hipError_t launch_conv_patch_fused(const MfmaShape& shape, const StageArgs& args, hipStream_t stream, LaunchEvents ev);
 
 // Launch a bf16 3-channel first layer with its 2x2/2 pool fused with the
 // 3x3 stage (32 -> 64 channels, fused pool) that follows it
@@ -204,7 +211,9 @@ hipError_t launch_conv_patch_first(const MfmaShape& shape, const StageArgs& args
 // 64 channels, one ring slot.
 #define MAFAT_FIRST_SHAPES           \
   MAFAT_FIRST(12, 16, 192, 4, 2)     \
-  MAFAT_FIRST(14, 18, 256, 4, 2)
+  MAFAT_FIRST(14, 18, 256, 4, 2)     \
+  MAFAT_FIRST(8, 16, 128, 4, 2)      \
+  MAFAT_FIRST(8, 8, 64, 4, 2)
 
 // Repack one layer's KRSC bf16 weights into the patch kernel's packed layout.
 hipError_t launch_pack_weights(const uint16_t* src, uint16_t* dst, int cout, int cin, int bn, int nblk,

@@ -839,7 +839,7 @@ __global__ __launch_bounds__(256) void pool_kernel(const StageArgs a) {
   typedef T Piece __attribute__((ext_vector_type(EPV)));
   KTile tl;
   const BlockPos bp = decode_block(a, &tl);
-  const int c_in = a.cin, per = c_in / EPV, bu = a.block_px;
+  const int c_in = a.cin, per = c_in / EPV, bu = a.block;
   const int f = F > 0 ? F : a.f;
   const T* src = static_cast<const T*>(a.src) + bp.frame * a.src_fstride + tl.src_off;
   T* dst = static_cast<T*>(a.dst) + bp.frame * a.dst_fstride + tl.dst_off;

@@ -4,6 +4,8 @@
 
 #include <array>
 #include <cstdint>
+#include <memory>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -77,12 +79,21 @@ struct Group {
 
 }  // namespace mafat
 
+namespace mafat {
+struct GroupRun;  // how a group runs for one batch and dtype (below)
+}  // namespace mafat
+
 struct mafat_plan {
   int n, in_h, in_w, in_c;
   std::vector<mafat_layer> layers;
   std::vector<std::array<int, 6>> dims;  // in_h, in_w, in_c, out_h, out_w, out_c
   std::vector<mafat::Group> groups;
   bool packed_weights = false;  // MAFAT_PLAN_PACKED_WEIGHTS
+  // The last few GroupRuns asked for, shared by the threads that use the plan
+  // (group_run); set_tile_batch empties it.
+  struct RunKey { int group, batch, dtype; };
+  mutable std::mutex run_mutex;
+  mutable std::vector<std::pair<RunKey, std::shared_ptr<const mafat::GroupRun>>> runs;
 };
 
 namespace mafat {
@@ -101,11 +112,11 @@ struct StageConfig {
   int fuse;          // 1: runs fused with the next (1x1) stage when both are launched
                      //    together; -1: the second stage of such a pair; 0: neither
 };
-StageConfig choose_config(const Stage& S, int batch, int dtype);
+// share: the part of the stage's tiles that one launch covers.
+StageConfig choose_config(const Stage& S, int batch, int dtype, double share);
 
-// The configuration a stage runs with in a plan (choose_config with the
-// batch the plan's weight layout fixes, and the generic kernel for frames
-// too large for 32-bit offsets).
+// The configuration a stage runs with in a plan (choose_config for the tiles
+// of a launch, and the generic kernel for frames too large for 32-bit offsets).
 StageConfig stage_config(const mafat_plan& P, const Group& G, const Stage& S, int batch, int dtype);
 
 // Packed weights of a conv layer (run by the bf16 3x3 patch kernel in a
@@ -131,6 +142,17 @@ struct BandLayout {
   int64_t frame;  // elements of one frame's bands
 };
 BandLayout band_layout(const mafat_plan& P, const Group& G, int dtype);
+
+// What a run of a group asks of the plan over and over: every stage's
+// configuration, the channel block of its packed weights (0: KRSC) and, with
+// row reuse, the bands.  Sizing a group's blocks takes longer on the host than
+// launching it, so the plan keeps the last few.
+struct GroupRun {
+  std::vector<StageConfig> cfgs;
+  std::vector<int> pack;
+  BandLayout bands;
+};
+std::shared_ptr<const GroupRun> group_run(const mafat_plan& P, int group, int batch, int dtype);
 
 // Every group of a plan in order (mafat_run_network without clearing the
 // error state), on the given workspace; stream is a hipStream_t.

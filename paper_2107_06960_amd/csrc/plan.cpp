@@ -698,6 +698,8 @@ extern "C" int mafat_plan_set_tile_batch(mafat_plan* plan, int32_t tiles) {
     }
   for (Group& G : plan->groups)
     if (!G.partition) set_tile_batch(G, (tiles == 0) ? G.ntiles : std::min<int>(tiles, G.ntiles));
+  const std::lock_guard<std::mutex> lock(plan->run_mutex);
+  plan->runs.clear();  // their blocks were sized for other launches
   return MAFAT_OK;
 }
 

@@ -142,6 +142,78 @@ void choose_any(const Stage& S, int batch, int dtype, StageConfig* c) {
   }
 }
 
+// Block shape of the bf16 3x3 patch kernel, by a model fitted to a sweep of
+// sixty layers (YOLOv2's 3x3 stages at 608x608 under six tilings and batches,
+// a VGG-style stack, layers of 13x13 to 304x304 with 32 to 512 channels;
+// twenty block shapes, the eleven that win anywhere kept; the chosen shape is
+// 2 % behind the measured best on average, 13 % at most): with n workgroups
+// per compute unit, of which occ share it, a launch takes ~2 us and the longer
+// of ceil(n / occ) rounds of x + v per 32-channel chunk (decode, first loads,
+// epilogue; the latency of a chunk) and x + u per chunk for each of them (the
+// unit's matrix cores and LDS).  So small launches take small blocks
+// (34x34 64->128, one tile: 4.1 us with 4x8 blocks of 32 channels, 7.0 us
+// with 16x16 of 64), launches of one round blocks that fill it, and larger
+// ones one-slot rings, whose workgroups share a unit and hide each other's
+// loads and epilogues (152x152 64->128 on sixteen tiles, eight frames: 40.8
+// us with 12x16 blocks, four waves and one slot, 52.3 us with 16x16 and two).
+void choose_patch(const Stage& S, int batch, double share, StageConfig* c) {
+  struct PS { int br, bc, bm, bn, wgm, wgn, ns, occ; double x, v, u; };
+  static const PS kPatch[] = {
+#define MAFAT_PATCH(br_, bc_, bm_, bn_, wgm_, wgn_, ns_, occ_, x_, v_, u_) \
+  {br_, bc_, bm_, bn_, wgm_, wgn_, ns_, occ_, x_, v_, u_},
+      MAFAT_PATCH_SHAPES
+#undef MAFAT_PATCH
+  };
+  const int chunks = S.cin / 32;
+  double best = 1e30;
+  for (const PS& r : kPatch) {
+    if (r.bn > S.cout && r.bn > 32) continue;
+    int64_t mb = 0;
+    for (const TileGeom& T : S.tiles)
+      mb += static_cast<int64_t>((T.ch + r.br - 1) / r.br) * ((T.cw + r.bc - 1) / r.bc);
+    const int64_t blocks = mb * ((S.cout + r.bn - 1) / r.bn);
+    const double n = static_cast<double>(blocks) * batch * share / 256.0;
+    const double t = std::max(std::ceil(n / r.occ) * (r.x + chunks * r.v),
+                              n > 1.0 ? r.x + std::ceil(n) * chunks * r.u : 0.0);
+    if (t < best) {
+      best = t;
+      c->br = r.br; c->bc = r.bc; c->bm = r.bm; c->bn = r.bn; c->wgm = r.wgm; c->wgn = r.wgn; c->depth = r.ns;
+      c->blocks = blocks;
+    }
+  }
+}
+
+// Channel block of a 3x3 layer's packed weights.  It is part of the packed
+// buffer's layout, so it must not follow the block shapes above: it is the one
+// of this rule on the plan's tiles (a stage takes ceil(workgroups / 256)
+// rounds of 3 us plus 0.18 ns per block pixel-channel and chunk; within 2 %
+// the fewer blocks), whatever the batch and the launches.
+int pack_block(const Stage& S) {
+  struct PB { int br, bc, bm, bn, ns; };
+  static const PB kPack[] = {{16, 16, 256, 64, 2}, {12, 12, 192, 64, 2}, {12, 16, 192, 64, 2}, {16, 12, 192, 64, 2},
+                             {10, 10, 128, 32, 2}, {8, 8, 64, 32, 2},    {8, 16, 128, 64, 1},  {12, 16, 192, 64, 1}};
+  const int chunks = S.cin / 32;
+  double best = 1e30;
+  int64_t best_blocks = 0;
+  int bn = 0;
+  for (const PB& r : kPack) {
+    if (r.bn > S.cout && r.bn > 32) continue;
+    if ((r.ns == 1) != (chunks == 1 && S.cout >= 64)) continue;
+    int64_t mb = 0;
+    for (const TileGeom& T : S.tiles)
+      mb += static_cast<int64_t>((T.ch + r.br - 1) / r.br) * ((T.cw + r.bc - 1) / r.bc);
+    const int64_t blocks = mb * ((S.cout + r.bn - 1) / r.bn);
+    const double rounds = std::ceil(static_cast<double>(blocks) / 256.0);
+    const double t = rounds * (3e-6 + chunks * static_cast<double>(r.bm) * r.bn * 0.18e-9);
+    if (t < best * 0.98 || (t < best * 1.02 && blocks < best_blocks)) {
+      best = t;
+      best_blocks = blocks;
+      bn = r.bn;
+    }
+  }
+  return bn;
+}
+
 // Block shape of the float32 3x3 split kernel: a launch takes rounds of one
 // workgroup per compute unit (two for the smallest shape's LDS), a round one
 // step per chunk and filter row plus ~2.4 us (decode, first loads, epilogue).
@@ -153,7 +225,7 @@ void choose_any(const Stage& S, int batch, int dtype, StageConfig* c) {
 // before: 3x3 128->256 on 76x76, four frames 160.6 -> 90.6 us; 208x208 32->64
 // on nine tiles 51.1 -> 35.0 us; 26x26 256->512 47.1 -> 32.3 us; 20x17 64->96
 // 11.7 -> 9.8 us.
-void choose_split(const Stage& S, int batch, StageConfig* c) {
+void choose_split(const Stage& S, int batch, double share, StageConfig* c) {
   struct SS { int br, bc, bm, bn, wgm, wgn; };
   static const SS kSplit[] = {
 #define MAFAT_SPLIT(br_, bc_, bm_, bn_, wgm_, wgn_) {br_, bc_, bm_, bn_, wgm_, wgn_},
@@ -166,7 +238,7 @@ void choose_split(const Stage& S, int batch, StageConfig* c) {
     for (const TileGeom& T : S.tiles)
       mb += static_cast<int64_t>((T.ch + r.br - 1) / r.br) * ((T.cw + r.bc - 1) / r.bc);
     const int64_t blocks = mb * ((S.cout + r.bn - 1) / r.bn);
-    const double wgs = static_cast<double>(blocks) * batch;
+    const double wgs = std::ceil(static_cast<double>(blocks) * batch * share);
     const bool two = r.bm == 64 && r.bn == 32;
     const double step = r.bm * r.bn == 128 * 64 ? (wgs > 256 ? 1.55 : 1.4)
                         : r.bm == 128           ? (r.br == 10 ? 1.16 : 1.13)
@@ -188,7 +260,7 @@ void choose_split(const Stage& S, int batch, StageConfig* c) {
 // flop/clock) and its operand traffic at the CU's L2 bandwidth (64
 // bytes/clock); workgroups beyond 256 queue on the CUs.  Larger tiles
 // re-read fewer operands, smaller ones give more workgroups.
-StageConfig choose_config(const Stage& S, int batch, int dtype) {
+StageConfig choose_config(const Stage& S, int batch, int dtype, double share) {
   StageConfig c{};
   c.bm = 64; c.bn = 64; c.depth = 3; c.kg = 1; c.wgm = 2; c.wgn = 2; c.br = 0; c.bc = 0;
   if (S.kind == STAGE_POOL) {
@@ -217,52 +289,10 @@ StageConfig choose_config(const Stage& S, int batch, int dtype) {
   const int esz = (dtype == MAFAT_BF16) ? 2 : 4;
   const double K = static_cast<double>(S.f) * S.f * S.cin;
   if (dtype == MAFAT_BF16 && S.f == 3) {
-    // 3x3 patch kernel (each block's input patch loaded once per 32-channel
-    // chunk and shared by the nine taps), 8 waves per workgroup (two per
-    // SIMD: LDS reads reach ~220 bytes/clock per CU only with more than one
-    // wave per SIMD).  Block shape by a model fitted to a sweep of the
-    // YOLOv2 stages at 608x608 (5x5/8/2x2): one workgroup per CU (the ring
-    // takes most of the LDS), so a stage takes ceil(workgroups / 256)
-    // rounds of ~3 us (decode, first loads, epilogue) plus, per 32-channel
-    // chunk, ~0.18 ns per block pixel-channel (edge blocks of a tile compute
-    // their full rectangle).  Large blocks waste work on small tiles and
-    // leave CUs idle on small stages; small blocks re-load more halo and
-    // weights.
     c.kind = K_CONV_PATCH;
-    struct PS { int br, bc, bm, bn, wgm, wgn, ns; };
-    static const PS kPatch[] = {
-#define MAFAT_PATCH(br_, bc_, bm_, bn_, wgm_, wgn_, ns_) {br_, bc_, bm_, bn_, wgm_, wgn_, ns_},
-        MAFAT_PATCH_SHAPES
-#undef MAFAT_PATCH
-    };
-    const int chunks = S.cin / 32;
-    double best = 1e30;
-    for (const PS& r : kPatch) {
-      // 128 channels: the fused layer 4-5 pair's shape; 14x18: a first-layer
-      // pair's shape (its second stage alone takes it too)
-      if ((r.bn > S.cout && r.bn > 32) || r.bn == 128 || r.br == 14) continue;
-      // One-slot rings only for single-chunk layers (c_in = 32), where they
-      // are measured fastest (several workgroups per CU overlap their loads);
-      // among them the model below picks (12x16 blocks on YOLOv2's layer 2
-      // at 608x608: 9.8 us against 12 us for 8x16).
-      if ((r.ns == 1) != (chunks == 1 && S.cout >= 64)) continue;
-      int64_t mb = 0;
-      for (const TileGeom& T : S.tiles)
-        mb += static_cast<int64_t>((T.ch + r.br - 1) / r.br) * ((T.cw + r.bc - 1) / r.bc);
-      const int64_t blocks = mb * ((S.cout + r.bn - 1) / r.bn);
-      const double rounds = std::ceil(static_cast<double>(blocks) * batch / 256.0);
-      const double t = rounds * (3e-6 + chunks * static_cast<double>(r.bm) * r.bn * 0.18e-9);
-      // Within 2 % of the best, fewer blocks win (less halo and weight
-      // traffic; e.g. 12x16 over 12x12 blocks, whose GEMM rows are padded
-      // from 144 to 192).
-      if (t < best * 0.98 || (t < best * 1.02 && blocks < c.blocks)) {
-        best = t;
-        c.br = r.br; c.bc = r.bc; c.bm = r.bm; c.bn = r.bn; c.wgm = r.wgm; c.wgn = r.wgn; c.depth = r.ns;
-        c.blocks = blocks;
-      }
-    }
+    choose_patch(S, batch, share, &c);
   }
-  if (dtype == MAFAT_BF16 && (S.f != 3 || c.kind != K_CONV_PATCH || c.br == 0)) {
+  if (dtype == MAFAT_BF16 && S.f != 3) {
     // LDS-ring kernel.  Block shapes from a sweep over every YOLOv2 stage
     // at 608x608 (tiling 5x5/8/2x2; blocks 32..128 x 32..128, ring depths
     // 2..8, one or two K groups): the K loop of a workgroup is bound by LDS
@@ -287,7 +317,7 @@ StageConfig choose_config(const Stage& S, int batch, int dtype) {
     c.blocks = mb * ((S.cout + c.bn - 1) / c.bn);
   } else if (dtype != MAFAT_BF16 && S.f == 3 && S.cin % 32 == 0) {
     c.kind = K_CONV_SPLIT;
-    choose_split(S, batch, &c);
+    choose_split(S, batch, share, &c);
   } else if (dtype != MAFAT_BF16) {
     c.kind = K_CONV_MFMA;
     const double clk = 2.4e9, mfma_rate = 4096.0 * clk, l2_rate = 64.0 * clk, t0 = 2e-6;
@@ -387,16 +417,18 @@ bool fused_first(const mafat_plan& P, const Group& G, int s, int dtype) {
   return static_cast<int64_t>(din[0]) * din[1] * din[2] * 2 < (1ll << 31);
 }
 
-StageConfig first_pair_config(const Stage& B, int batch) {
+StageConfig first_pair_config(const Stage& B, int batch, double share) {
   // Blocks of the 3x3 stage's conv outputs, all 64 channels, 4x2 waves, one
-  // ring slot: 12x16 (48x32 per wave) or 14x18 (64x32 per wave, 256 GEMM
-  // rows for 252 outputs).  Two workgroups fit a CU (LDS), so a launch takes
-  // ceil(blocks / 512) rounds; a workgroup costs a fixed ~2.5 us (decode,
-  // input and weight latency, epilogue) plus ~0.027 us per GEMM row
-  // (per-workgroup timestamps at 608x608, 5x5 tiles, where 14x18 blocks
-  // make 500 workgroups, one round, and 12x16 blocks 720, two).
-  struct FS { int br, bc, bm; };
-  static const FS kShapes[] = {{12, 16, 192}, {14, 18, 256}};
+  // ring slot: 8x8 to 14x18 (256 GEMM rows for 252 outputs).  By a model of
+  // the launch times at 608x608 (5x5 tiles) and of a 72x72 tile, 1 to 25
+  // frames: with n workgroups per compute unit, `one` us up to n = 1, `more`
+  // us for each of the next few, which share the unit, and `each` us for each
+  // once it is full.  One 72x72 tile: 5.6 / 6.4 / 7.2 / 8.2 us with 64, 128,
+  // 192 and 256 rows; twenty-five tiles at 608x608: 17.6 / 13.9 / 14.6 / 12.4
+  // us; with eight frames 100 / 69 / 69 / 74 us.
+  struct FS { int br, bc, bm; double one, more, each; };
+  static const FS kShapes[] = {
+      {8, 8, 64, 5.6, 2.0, 2.1}, {8, 16, 128, 6.5, 2.6, 1.67}, {12, 16, 192, 7.3, 3.4, 2.9}, {14, 18, 256, 8.3, 4.1, 4.5}};
   StageConfig c{};
   c.kind = K_CONV_PATCH;
   c.bn = 64; c.wgm = 4; c.wgn = 2; c.depth = 1; c.kg = 1; c.kord = 1; c.chan_major = 0;
@@ -405,8 +437,8 @@ StageConfig first_pair_config(const Stage& B, int batch) {
     int64_t mb = 0;
     for (const TileGeom& T : B.tiles)
       mb += static_cast<int64_t>((T.ch + f.br - 1) / f.br) * ((T.cw + f.bc - 1) / f.bc);
-    const double rounds = std::ceil(static_cast<double>(mb) * batch / 512.0);
-    const double t = rounds * (2.5 + 0.027 * f.bm);
+    const double n = static_cast<double>(mb) * batch * share / 256.0;
+    const double t = std::max(f.one + f.more * std::max(std::min(std::ceil(n), 4.0) - 1.0, 0.0), 4.0 + f.each * n);
     if (t < best) {
       best = t;
       c.br = f.br; c.bc = f.bc; c.bm = f.bm; c.blocks = mb;
@@ -419,36 +451,44 @@ StageConfig first_pair_config(const Stage& B, int batch) {
 
 StageConfig stage_config(const mafat_plan& P, const Group& G, const Stage& S, int batch, int dtype) {
   const int si = static_cast<int>(&S - G.stages.data());
+  // the part of the group's tiles that one launch covers
+  const double share = static_cast<double>(std::min({G.tile_batch, G.ntiles, kMaxTilesPerLaunch})) / G.ntiles;
   if (fused_first(P, G, si, dtype)) {
     // its own configuration (the first-layer kernel) when it runs alone;
     // run together with the next stage, the launch takes the pair's shape
-    StageConfig c = choose_config(S, P.packed_weights ? 1 : batch, dtype);
+    StageConfig c = choose_config(S, batch, dtype, share);
     c.fuse = 2;
     return c;
   }
   if (fused_first(P, G, si - 1, dtype)) {
-    // run alone (mafat_run_stage) it takes the fused kernel's block shape,
-    // so its packed weights serve both
-    StageConfig c = first_pair_config(S, P.packed_weights ? 1 : batch);
+    // run alone (mafat_run_stage) it takes the fused kernel's block shape
+    StageConfig c = first_pair_config(S, batch, share);
     c.fuse = -2;
     return c;
   }
   if (fused_pair(P, G, si, dtype)) {
-    // 8x16 blocks of all 128 channels, one ring slot (the weights of a
-    // 32-channel chunk take 72 KiB): on YOLOv2's layer 4 at 608x608 with
-    // 5x5 tiles one workgroup per CU, in one round.
+    // 8x16 or 8x8 blocks of all 128 channels, one ring slot (the weights of a
+    // 32-channel chunk take 72 KiB, so one workgroup per compute unit): a
+    // round of the former takes 8.5 us, of the latter 6.3 us.  On YOLOv2's
+    // layers 4-5 at 608x608 with 5x5 tiles the former make one round; a 36x36
+    // tile takes 8.8 us with them and 7.2 us with the latter.
     StageConfig c{};
     c.kind = K_CONV_PATCH;
-    c.br = 8; c.bc = 16; c.bm = 128; c.bn = 128; c.wgm = 4; c.wgn = 2; c.depth = 1; c.kg = 1; c.kord = 1;
-    int64_t mb = 0;
-    for (const TileGeom& T : S.tiles) mb += static_cast<int64_t>((T.ch + 7) / 8) * ((T.cw + 15) / 16);
-    c.blocks = mb;
+    c.br = 8; c.bn = 128; c.wgm = 4; c.wgn = 2; c.depth = 1; c.kg = 1; c.kord = 1;
+    double best = 1e30;
+    for (const int bc : {16, 8}) {
+      int64_t mb = 0;
+      for (const TileGeom& T : S.tiles) mb += static_cast<int64_t>((T.ch + 7) / 8) * ((T.cw + bc - 1) / bc);
+      const double t = std::ceil(static_cast<double>(mb) * batch * share / 256.0) * (bc == 16 ? 8.5 : 6.3);
+      if (t < best) {
+        best = t;
+        c.bc = bc; c.bm = 8 * bc; c.blocks = mb;
+      }
+    }
     c.fuse = 1;
     return c;
   }
-  // A plan with packed weights fixes the layout for every batch: its
-  // stages take the configuration chosen for one frame.
-  StageConfig c = choose_config(S, P.packed_weights ? 1 : batch, dtype);
+  StageConfig c = choose_config(S, batch, dtype, share);
   if (fused_pair(P, G, si - 1, dtype)) c.fuse = -1;
   // The matrix-core kernels address a frame's source buffer with 32-bit
   // byte offsets; the generic kernel covers larger frames.
@@ -471,8 +511,9 @@ bool packed_layout(const mafat_plan& P, int layer, int dtype, int* bn, int* nblk
       if (S.kind == STAGE_CONV && S.first == layer) {
         const StageConfig c = stage_config(P, G, S, 1, dtype);
         if (c.kind != K_CONV_PATCH) return false;
-        *bn = c.bn;
-        *nblk = (S.cout + c.bn - 1) / c.bn;
+        // the fused pairs' 3x3 layers: all their channels
+        *bn = c.fuse == 1 ? 128 : c.fuse == -2 ? 64 : pack_block(S);
+        *nblk = (S.cout + *bn - 1) / *bn;
         *nchunk = S.cin / 32;
         return true;
       }
@@ -496,9 +537,32 @@ BandLayout band_layout(const mafat_plan& P, const Group& G, int dtype) {
   return B;
 }
 
+std::shared_ptr<const GroupRun> group_run(const mafat_plan& P, int group, int batch, int dtype) {
+  const size_t kKept = std::max<size_t>(16, 4 * P.groups.size());
+  {
+    const std::lock_guard<std::mutex> lock(P.run_mutex);
+    for (const auto& r : P.runs)
+      if (r.first.group == group && r.first.batch == batch && r.first.dtype == dtype) return r.second;
+  }
+  const Group& G = P.groups[static_cast<size_t>(group)];
+  auto R = std::make_shared<GroupRun>();
+  for (const Stage& S : G.stages) {
+    R->cfgs.push_back(stage_config(P, G, S, batch, dtype));
+    int bn, nblk, nchunk;
+    packed_layout(P, S.first, dtype, &bn, &nblk, &nchunk);
+    R->pack.push_back(bn);
+  }
+  if (G.reuse) R->bands = band_layout(P, G, dtype);
+  const std::lock_guard<std::mutex> lock(P.run_mutex);
+  if (P.runs.size() >= kKept) P.runs.erase(P.runs.begin());
+  P.runs.emplace_back(mafat_plan::RunKey{group, batch, dtype}, R);
+  return R;
+}
+
 WorkspaceLayout workspace_layout(const mafat_plan& P, const Group& G, int batch, int dtype) {
   const size_t esz = (dtype == MAFAT_F32) ? 4 : 2;
-  const int64_t frame = G.reuse ? band_layout(P, G, dtype).frame : G.scratch_frame;
+  const int64_t frame =
+      G.reuse ? group_run(P, static_cast<int>(&G - P.groups.data()), batch, dtype)->bands.frame : G.scratch_frame;
   WorkspaceLayout L{};
   L.scratch = (static_cast<size_t>(batch) * frame * esz + 255) & ~static_cast<size_t>(255);
   L.total = L.scratch;
@@ -598,8 +662,9 @@ int run_group_impl(const mafat_plan* plan, int g, int s_begin, int s_end, int ba
   const auto& dout = plan->dims[G.l1];
   const int64_t in_frame = static_cast<int64_t>(din[0]) * din[1] * din[2];
   const int64_t out_frame = static_cast<int64_t>(dout[3]) * dout[4] * dout[5];
-  BandLayout bands;
-  if (G.reuse) bands = band_layout(*plan, G, dtype);
+  const std::shared_ptr<const GroupRun> plan_run = group_run(*plan, g, batch, dtype);
+  const std::vector<StageConfig>& cfgs = plan_run->cfgs;
+  const BandLayout& bands = plan_run->bands;
   const int64_t scr_frame = G.reuse ? bands.frame : G.scratch_frame;
   if (in_frame >= (1ll << 31) || out_frame >= (1ll << 31) || scr_frame >= (1ll << 31))
     return fail(MAFAT_EUNSUPPORTED, "a frame's tensor exceeds 2^31 elements");
@@ -617,6 +682,7 @@ int run_group_impl(const mafat_plan* plan, int g, int s_begin, int s_end, int ba
         return fail(MAFAT_EINVAL, "layer " + std::to_string(l) + ": weights, scale or bias not 16-byte aligned");
     }
 
+  const int ns_all = static_cast<int>(G.stages.size());
   // Tile batches (mafat_plan_set_tile_batch): tiles [b0, b0 + K) go through
   // all stages, then the next K tiles; the workspace holds K tiles.
   const int K = G.tile_batch;
@@ -627,7 +693,6 @@ int run_group_impl(const mafat_plan* plan, int g, int s_begin, int s_end, int ba
   // that launch of row i - 1 (the first after the band's reader, which
   // neither reads nor writes it); -1: row i's first launch (it reads the
   // group input and writes another band); -2: a copy launch of its own.
-  const int ns_all = static_cast<int>(G.stages.size());
   std::vector<int> launch_of(static_cast<size_t>(ns_all), 0), carrier(static_cast<size_t>(ns_all), -2);
   int nlaunch = 0;
   struct BandCopy { int64_t src, dst, bytes; bool aligned; };
@@ -662,8 +727,7 @@ int run_group_impl(const mafat_plan* plan, int g, int s_begin, int s_end, int ba
   };
   if (G.reuse) {
     for (int s = s_begin; s < s_end; ++s) {
-      const bool fz = stage_config(*plan, G, G.stages[static_cast<size_t>(s)], batch, dtype).fuse > 0 &&
-                      s + 1 < s_end;
+      const bool fz = cfgs[static_cast<size_t>(s)].fuse > 0 && s + 1 < s_end;
       launch_of[static_cast<size_t>(s)] = nlaunch;
       if (fz) launch_of[static_cast<size_t>(++s)] = nlaunch;
       ++nlaunch;
@@ -724,7 +788,7 @@ int run_group_impl(const mafat_plan* plan, int g, int s_begin, int s_end, int ba
       hipEvent_t ev_start = events ? static_cast<hipEvent_t>(events[2 * (s - s_begin)]) : nullptr;
       hipEvent_t ev_stop = events ? static_cast<hipEvent_t>(events[2 * (s - s_begin) + 1]) : nullptr;
       bool launched = started[static_cast<size_t>(s - s_begin)] != 0;
-      const StageConfig scfg = stage_config(*plan, G, S, batch, dtype);
+      const StageConfig& scfg = cfgs[static_cast<size_t>(s)];
       // Both stages of a fused pair in this call: one kernel for the two
       // (the second stage's interval is recorded empty, after it).  A
       // first-layer pair (fuse 2) computes the second stage's blocks, its
@@ -732,7 +796,7 @@ int run_group_impl(const mafat_plan* plan, int g, int s_begin, int s_end, int ba
       const bool fuse = scfg.fuse > 0 && s + 1 < s_end;
       const bool first = fuse && scfg.fuse == 2;
       const Stage* S2 = fuse ? &G.stages[s + 1] : nullptr;
-      const StageConfig cfg = first ? first_pair_config(*S2, batch) : scfg;
+      const StageConfig cfg = first ? cfgs[static_cast<size_t>(s + 1)] : scfg;
       const Stage& SC = first ? *S2 : S;  // the convolution whose GEMM the launch computes
       const int kind = cfg.kind;
       const bool matrix = (kind == K_CONV_MFMA || kind == K_CONV_RING || kind == K_CONV_PATCH || kind == K_CONV_ANY ||
@@ -775,8 +839,7 @@ int run_group_impl(const mafat_plan* plan, int g, int s_begin, int s_end, int ba
       A.act = SC.act;
       A.nblk_n = matrix ? (SC.cout + shape.bn - 1) / shape.bn : 1;
       A.chan_major = matrix ? cfg.chan_major : 0;
-      A.block_px = bu;
-      A.w_packed = (plan->packed_weights && kind == K_CONV_PATCH) ? 1 : 0;
+      A.block = (kind == K_CONV_PATCH) ? plan_run->pack[static_cast<size_t>(first ? s + 1 : s)] : (kind == K_POOL) ? bu : 0;
       for (int t0 = b0; t0 < b1; t0 += kMaxTilesPerLaunch) {
         const int t1 = std::min(b1, t0 + kMaxTilesPerLaunch);
         A.ntiles = t1 - t0;
@@ -858,7 +921,7 @@ int run_group_impl(const mafat_plan* plan, int g, int s_begin, int s_end, int ba
         } else if (first) {
           e = launch_conv_patch_first(shape, A, stream, lev);
         } else if (fuse) {
-          e = launch_conv_patch_fused(A, stream, lev);
+          e = launch_conv_patch_fused(shape, A, stream, lev);
         } else if (kind == K_CONV_PATCH) {
           e = launch_conv_patch(S.pool, shape, A, stream, lev);
         } else if (kind == K_CONV_SPLIT) {
@@ -1051,7 +1114,7 @@ extern "C" int mafat_plan_stage_kernel(const mafat_plan* plan, int32_t group, in
 extern "C" int mafat_debug_config(const mafat_plan* plan, int32_t g, int32_t s, int32_t batch, int32_t dtype,
                                   int32_t* out) {
   const mafat::Stage& S = plan->groups[g].stages[s];
-  const mafat::StageConfig c = mafat::choose_config(S, batch, dtype);
+  const mafat::StageConfig c = mafat::choose_config(S, batch, dtype, 1.0);
   const int32_t v[8] = {c.kind, c.bm, c.bn, c.depth, c.kg, c.kord, c.br, c.bc};
   for (int k = 0; k < 8; ++k) out[k] = v[k];
   return 0;
