@@ -295,7 +295,7 @@ void conv_patch_kernel(const StageArgs a) {
   MAFAT_PTRACE(1 + (tl.ch < -1 ? 1 : 0));
   const int wm = wave / WGN, wn = wave - wm * WGN;
   const int nbx = (tl.cw + BC - 1) / BC;
-  const int bby = bp.mb / nbx, bbx = bp.mb - bby * nbx;
+  const int bby = div_small(bp.mb, nbx), bbx = bp.mb - bby * nbx;
   const int by0 = tl.cy0 + bby * BR, bx0 = tl.cx0 + bbx * BC;  // block origin (conv outputs)
   const int n0 = bp.nb * BN;
   const int sw = tl.sw;

@@ -100,7 +100,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void conv_split_kernel(const StageA
   KTile tl;
   const BlockPos bp = decode_block(a, &tl);
   const int nbx = (tl.cw + BC - 1) / BC;
-  const int bby = bp.mb / nbx, bbx = bp.mb - bby * nbx;
+  const int bby = div_small(bp.mb, nbx), bbx = bp.mb - bby * nbx;
   const int by0 = tl.cy0 + bby * BR, bx0 = tl.cx0 + bbx * BC;  // block origin (conv outputs)
   const int n0 = bp.nb * BN;
   const float* src = static_cast<const float*>(a.src) + bp.frame * a.src_fstride + tl.src_off;

@@ -86,6 +86,21 @@ struct BlockPos {
 struct NoEarly {
   __device__ void operator()(int) const {}
 };
+// n / d for 0 <= n < 2^31 with the host's multiplier (set_div in run.cpp): a
+// division by a number known only at run time takes some thirty instructions
+// ahead of a workgroup's first load.
+__device__ __forceinline__ int div_by(int n, uint32_t mul, int shift) {
+  return static_cast<int>(__umulhi(2u * static_cast<uint32_t>(n), mul) >> shift);
+}
+// n / d for a quotient below 2^19 (d > 0, n >= 0): the float quotient is off by
+// less than one.
+__device__ __forceinline__ int div_small(int n, int d) {
+  int q = static_cast<int>(static_cast<float>(n) * __builtin_amdgcn_rcpf(static_cast<float>(d)));
+  const int r = n - q * d;
+  q += r >= d ? 1 : 0;
+  q -= r < 0 ? 1 : 0;
+  return q;
+}
 // One lane's entry of the per-tile tables.
 struct TileTable {
   int pre;
@@ -111,15 +126,15 @@ __device__ __forceinline__ BlockPos locate_block(const StageArgs& a, const TileT
   const int bid = xcd_remap(workgroup, a.total_blocks);
   const int per_frame = a.mblk_total * a.nblk_n;
   BlockPos p;
-  p.frame = bid / per_frame;
+  p.frame = div_by(bid, a.div_frame, a.shift_frame);
   const int blk = bid - p.frame * per_frame;
   // channel blocks then pixel blocks (or the other way round)
   int mg;
   if (a.chan_major) {
-    p.nb = blk / a.mblk_total;
+    p.nb = div_by(blk, a.div_inner, a.shift_inner);
     mg = blk - p.nb * a.mblk_total;
   } else {
-    mg = blk / a.nblk_n;
+    mg = div_by(blk, a.div_inner, a.shift_inner);
     p.nb = blk - mg * a.nblk_n;
   }
   early(p.nb);

@@ -68,6 +68,10 @@ struct StageArgs {
   int64_t copy_fstride;
   int64_t copy_src[kMaxCarriedCopies], copy_dst[kMaxCarriedCopies], copy_bytes[kMaxCarriedCopies];
   int32_t copy_blocks, ncopy, copy_frames;
+  // Division by mblk_total * nblk_n and by the inner block count (nblk_n, or
+  // mblk_total when chan_major): n / d = mulhi(2 n, mul) >> shift for n < 2^31.
+  uint32_t div_frame, div_inner;
+  int32_t shift_frame, shift_inner;
   int32_t mblk_prefix[kMaxTilesPerLaunch + 1];
   KTile tiles[kMaxTilesPerLaunch];
 };

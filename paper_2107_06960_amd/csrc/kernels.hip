@@ -654,7 +654,7 @@ __global__ __launch_bounds__(256) void conv_rgb_mfma_kernel(const StageArgs a) {
   const BlockPos bp = decode_block(a, &tl);
   MAFAT_TRACE(4 + (tl.ch > 30000 ? 1 : 0));
   const int nbx = (tl.cw + BC - 1) / BC;
-  const int by = bp.mb / nbx, bx = bp.mb - by * nbx;
+  const int by = div_small(bp.mb, nbx), bx = bp.mb - by * nbx;
   const int oy0 = tl.cy0 + by * BR, ox0 = tl.cx0 + bx * BC;
   uint16_t* dst = static_cast<uint16_t*>(a.dst) + bp.frame * a.dst_fstride + tl.dst_off;
   const int kq = lane >> 4;

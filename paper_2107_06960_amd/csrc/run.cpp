@@ -637,6 +637,17 @@ void dump_launch_trace(int kind, const Stage& S, const MfmaShape& shape, const S
 }
 #endif
 
+// Multiplier and shift with n / d = (2 n * mul >> 32) >> shift for 0 <= n < 2^31
+// (d >= 1; a launch of no blocks has d = 0 and uses none): with 2^l the power
+// of two at or above d, mul = floor(2^(31 + l) / d) + 1 exceeds 2^(31 + l) / d
+// by at most 1, which changes a quotient of n < 2^31 by less than 1 / d.
+void set_div(int64_t d, uint32_t* mul, int32_t* shift) {
+  int l = 0;
+  while ((1ll << l) < d) ++l;
+  *mul = d > 0 ? static_cast<uint32_t>((1ull << (31 + l)) / static_cast<uint64_t>(d) + 1) : 0;
+  *shift = l;
+}
+
 // Runs stages [s_begin, s_end) of group g: per tile batch (all tiles
 // unless the plan sets fewer), every stage in order, a stage as one launch
 // per 64 tiles; a fused pair whose two stages are both in the range as one
@@ -883,6 +894,8 @@ int run_group_impl(const mafat_plan* plan, int g, int s_begin, int s_end, int ba
         const int64_t blocks = total * A.nblk_n * batch;
         if (blocks >= (1ll << 31)) return fail(MAFAT_EUNSUPPORTED, "grid too large");
         A.total_blocks = static_cast<int32_t>(blocks);
+        set_div(total * A.nblk_n, &A.div_frame, &A.shift_frame);
+        set_div(A.chan_major ? total : A.nblk_n, &A.div_inner, &A.shift_inner);
         const bool last_chunk = last_batch && t1 >= b1;
         const LaunchEvents lev{launched ? nullptr : ev_start, last_chunk ? ev_stop : nullptr};
         // carried copies: in the first chunk of the launch, as extra
