@@ -51,7 +51,8 @@ struct Stage {
   int out_h, out_w, cout;  // output tensor of the last layer
   int f, s, p, act;        // filter, stride, padding (conv or pool), activation (conv)
   int src_buf, dst_buf;    // BufKind
-  std::vector<TileGeom> tiles;
+  std::vector<TileGeom> tiles;  // row-major; rows of one height, columns of one width
+  int cols;                     // tiles per row
   // Row reuse (an output that is not the group's): per tile row i, the
   // first row of its output band (band_lo[i]) and the rows it computes,
   // [row_b[i], row_b[i + 1]) of the stage output; band_rows = the largest

@@ -152,6 +152,7 @@ int build_group(mafat_plan& plan, int g0, int g1, int rows, int cols, bool parti
     const auto& dout = plan.dims[S.last];
     S.in_h = din[0]; S.in_w = din[1]; S.cin = din[2];
     S.out_h = dout[3]; S.out_w = dout[4]; S.cout = dout[5];
+    S.cols = cols;
     G.stages.push_back(S);
     l = S.last + 1;
   }

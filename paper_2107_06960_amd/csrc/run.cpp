@@ -57,6 +57,15 @@ bool rgb_ok(const Stage& S) {
          (S.cout == 8 || S.cout == 16 || S.cout == 32 || S.cout == 64);
 }
 
+// br x bc pixel blocks over all of a stage's computed rectangles (their
+// heights depend on the tile row only, their widths on the column).
+int64_t pixel_blocks(const Stage& S, int br, int bc) {
+  int64_t nr = 0, nc = 0;
+  for (size_t t = 0; t < S.tiles.size(); t += static_cast<size_t>(S.cols)) nr += (S.tiles[t].ch + br - 1) / br;
+  for (int j = 0; j < S.cols; ++j) nc += (S.tiles[static_cast<size_t>(j)].cw + bc - 1) / bc;
+  return nr * nc;
+}
+
 // The any-filter matrix-core kernel: any filter, stride, padding and channel
 // counts whose weights are addressable with 32-bit byte offsets.
 bool any_ok(const Stage& S, int dtype) {
@@ -168,9 +177,7 @@ void choose_patch(const Stage& S, int batch, double share, StageConfig* c) {
   double best = 1e30;
   for (const PS& r : kPatch) {
     if (r.bn > S.cout && r.bn > 32) continue;
-    int64_t mb = 0;
-    for (const TileGeom& T : S.tiles)
-      mb += static_cast<int64_t>((T.ch + r.br - 1) / r.br) * ((T.cw + r.bc - 1) / r.bc);
+    const int64_t mb = pixel_blocks(S, r.br, r.bc);
     const int64_t blocks = mb * ((S.cout + r.bn - 1) / r.bn);
     const double n = static_cast<double>(blocks) * batch * share / 256.0;
     const double t = std::max(std::ceil(n / r.occ) * (r.x + chunks * r.v),
@@ -199,9 +206,7 @@ int pack_block(const Stage& S) {
   for (const PB& r : kPack) {
     if (r.bn > S.cout && r.bn > 32) continue;
     if ((r.ns == 1) != (chunks == 1 && S.cout >= 64)) continue;
-    int64_t mb = 0;
-    for (const TileGeom& T : S.tiles)
-      mb += static_cast<int64_t>((T.ch + r.br - 1) / r.br) * ((T.cw + r.bc - 1) / r.bc);
+    const int64_t mb = pixel_blocks(S, r.br, r.bc);
     const int64_t blocks = mb * ((S.cout + r.bn - 1) / r.bn);
     const double rounds = std::ceil(static_cast<double>(blocks) / 256.0);
     const double t = rounds * (3e-6 + chunks * static_cast<double>(r.bm) * r.bn * 0.18e-9);
@@ -234,9 +239,7 @@ void choose_split(const Stage& S, int batch, double share, StageConfig* c) {
   };
   double best = 1e30;
   for (const SS& r : kSplit) {
-    int64_t mb = 0;
-    for (const TileGeom& T : S.tiles)
-      mb += static_cast<int64_t>((T.ch + r.br - 1) / r.br) * ((T.cw + r.bc - 1) / r.bc);
+    const int64_t mb = pixel_blocks(S, r.br, r.bc);
     const int64_t blocks = mb * ((S.cout + r.bn - 1) / r.bn);
     const double wgs = std::ceil(static_cast<double>(blocks) * batch * share);
     const bool two = r.bm == 64 && r.bn == 32;
@@ -434,9 +437,7 @@ StageConfig first_pair_config(const Stage& B, int batch, double share) {
   c.bn = 64; c.wgm = 4; c.wgn = 2; c.depth = 1; c.kg = 1; c.kord = 1; c.chan_major = 0;
   double best = 1e30;
   for (const FS& f : kShapes) {
-    int64_t mb = 0;
-    for (const TileGeom& T : B.tiles)
-      mb += static_cast<int64_t>((T.ch + f.br - 1) / f.br) * ((T.cw + f.bc - 1) / f.bc);
+    const int64_t mb = pixel_blocks(B, f.br, f.bc);
     const double n = static_cast<double>(mb) * batch * share / 256.0;
     const double t = std::max(f.one + f.more * std::max(std::min(std::ceil(n), 4.0) - 1.0, 0.0), 4.0 + f.each * n);
     if (t < best) {
@@ -477,8 +478,7 @@ StageConfig stage_config(const mafat_plan& P, const Group& G, const Stage& S, in
     c.br = 8; c.bn = 128; c.wgm = 4; c.wgn = 2; c.depth = 1; c.kg = 1; c.kord = 1;
     double best = 1e30;
     for (const int bc : {16, 8}) {
-      int64_t mb = 0;
-      for (const TileGeom& T : S.tiles) mb += static_cast<int64_t>((T.ch + 7) / 8) * ((T.cw + bc - 1) / bc);
+      const int64_t mb = pixel_blocks(S, 8, bc);
       const double t = std::ceil(static_cast<double>(mb) * batch * share / 256.0) * (bc == 16 ? 8.5 : 6.3);
       if (t < best) {
         best = t;
@@ -503,6 +503,13 @@ StageConfig stage_config(const mafat_plan& P, const Group& G, const Stage& S, in
   return c;
 }
 
+// Channel block of the packed weights of a stage that runs as c (a patch
+// kernel's, whatever the batch): the fused pairs' 3x3 layers take all their
+// channels.
+static int stage_pack_block(const Stage& S, const StageConfig& c) {
+  return c.fuse == 1 ? 128 : c.fuse == -2 ? 64 : pack_block(S);
+}
+
 bool packed_layout(const mafat_plan& P, int layer, int dtype, int* bn, int* nblk, int* nchunk) {
   *bn = *nblk = *nchunk = 0;
   if (!P.packed_weights || dtype != MAFAT_BF16) return false;
@@ -511,8 +518,7 @@ bool packed_layout(const mafat_plan& P, int layer, int dtype, int* bn, int* nblk
       if (S.kind == STAGE_CONV && S.first == layer) {
         const StageConfig c = stage_config(P, G, S, 1, dtype);
         if (c.kind != K_CONV_PATCH) return false;
-        // the fused pairs' 3x3 layers: all their channels
-        *bn = c.fuse == 1 ? 128 : c.fuse == -2 ? 64 : pack_block(S);
+        *bn = stage_pack_block(S, c);
         *nblk = (S.cout + *bn - 1) / *bn;
         *nchunk = S.cin / 32;
         return true;
@@ -547,10 +553,9 @@ std::shared_ptr<const GroupRun> group_run(const mafat_plan& P, int group, int ba
   const Group& G = P.groups[static_cast<size_t>(group)];
   auto R = std::make_shared<GroupRun>();
   for (const Stage& S : G.stages) {
-    R->cfgs.push_back(stage_config(P, G, S, batch, dtype));
-    int bn, nblk, nchunk;
-    packed_layout(P, S.first, dtype, &bn, &nblk, &nchunk);
-    R->pack.push_back(bn);
+    const StageConfig c = stage_config(P, G, S, batch, dtype);
+    R->cfgs.push_back(c);
+    R->pack.push_back(P.packed_weights && c.kind == K_CONV_PATCH ? stage_pack_block(S, c) : 0);
   }
   if (G.reuse) R->bands = band_layout(P, G, dtype);
   const std::lock_guard<std::mutex> lock(P.run_mutex);
