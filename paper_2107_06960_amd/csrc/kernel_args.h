@@ -86,7 +86,8 @@ enum KernelKind {
   K_CONV_RING = 5,      // matrix cores, operands streamed into an LDS ring (bf16)
   K_CONV_PATCH = 6,     // 3x3 on the matrix cores, input patch shared by the taps (bf16)
   K_CONV_ANY = 7,       // matrix cores, any filter, stride, padding and channels
-  K_CONV_SPLIT = 8      // float32 3x3 on the bf16 matrix cores, operands in three parts
+  K_CONV_SPLIT = 8,     // float32 3x3 on the bf16 matrix cores, operands in three parts
+  K_CONV_THIN = 9       // matrix cores, input channels that fill no 16-byte piece, the patch in LDS
 };
 
 // Conv outputs (rows x columns) per workgroup of the matrix-core first-layer
@@ -155,6 +156,33 @@ struct MfmaShape {
 #define MAFAT_RING_TUNE_SHAPES
 #endif
 
+// Instantiated thin-input kernel shapes: (br, bc, bn).
+#define MAFAT_THIN_SHAPES                                                                \
+  MAFAT_THIN(16, 16, 64) MAFAT_THIN(16, 16, 32) MAFAT_THIN(8, 8, 64) MAFAT_THIN(8, 8, 32)
+
+// LDS of the thin-input kernel (bytes): a table entry per 16-byte piece of K
+// (bf16) or per value (fp32), the weights as they are in memory, and the
+// patch (rows rows of row_vals values, row_bytes apart), each with the bytes a
+// lane may read past its piece.
+constexpr int kThinLds = 64 * 1024;
+struct ThinLayout {
+  int run, steps;  // bf16: pieces per filter row; MFMA steps (of four pieces, or of four values)
+  int rows, row_vals, row_bytes;
+  int weights, patch, total;
+};
+__host__ __device__ inline ThinLayout thin_layout(int br, int bc, int bn, int f, int s, int cin, int esz) {
+  ThinLayout L;
+  L.run = (f * cin + 7) / 8;
+  L.steps = esz == 2 ? (f * L.run + 3) / 4 : (f * f * cin + 3) / 4;
+  L.rows = (br - 1) * s + f;
+  L.row_vals = ((bc - 1) * s + f) * cin;
+  L.row_bytes = (L.row_vals * esz + 7) / 8 * 8 + 4;  // an odd number of words: rows on other banks
+  L.weights = 4 * L.steps * (esz == 2 ? 32 : 4);
+  L.patch = L.weights + (bn * f * f * cin * esz + 32 + 15) / 16 * 16;
+  L.total = (L.patch + L.rows * L.row_bytes + 32 + 15) / 16 * 16;
+  return L;
+}
+
 // Instantiated split kernel shapes: (br, bc, bm, bn, wgm, wgn).
 #define MAFAT_SPLIT_SHAPES           \
   MAFAT_SPLIT(8, 16, 128, 64, 4, 2)  \
@@ -186,6 +214,10 @@ hipError_t launch_conv_ring(int f, bool pool, const MfmaShape& shape, const Stag
 // Launch one float32 3x3 split-operand stage chunk (conv_split.hip).
 hipError_t launch_conv_split(bool pool, const MfmaShape& shape, const StageArgs& args, hipStream_t stream,
                              LaunchEvents ev);
+
+// Launch one thin-input stage chunk (conv_thin.hip).
+hipError_t launch_conv_thin(int dtype, bool pool, const MfmaShape& shape, const StageArgs& args, hipStream_t stream,
+                            LaunchEvents ev);
 
 // Launch one any-filter matrix-core convolution stage chunk (conv_any.hip).
 hipError_t launch_conv_any(int dtype, bool pool, const MfmaShape& shape, const StageArgs& args, hipStream_t stream,

@@ -17,8 +17,8 @@
 //                       32-bit byte offsets (the other kernels' buffer
 //                       descriptors): one thread per output pixel (or per 2x2
 //                       pool window), weights through the scalar cache.
-//   conv_rgb_kernel     the 3-channel first layer on the vector ALUs
-//                       (fp32), patch in registers.
+//   conv_rgb_kernel     the 3-channel first layer on the vector ALUs, patch in
+//                       registers, for frames past 32-bit byte offsets.
 //   conv_rgb_mfma_kernel  the 3-channel first layer in bf16 on the matrix
 //                       cores, K = 27 zero-padded to 32.
 //   pool_kernel         a max-pool stage that does not follow a convolution.

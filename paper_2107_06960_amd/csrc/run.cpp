@@ -106,6 +106,28 @@ StageConfig tune_override(const Stage& S, StageConfig c) {
   return c;
 }
 
+// The thin-input kernel (input channels that fill no 16-byte piece): 16x16
+// blocks where they make two workgroups per compute unit, 8x8 ones otherwise
+// or where the patch needs it; all channels up to 64.  Whether a layer takes
+// it depends on the layer alone.
+bool choose_thin(const Stage& S, int batch, int dtype, double share, StageConfig* c) {
+  const int esz = (dtype == MAFAT_BF16) ? 2 : 4;
+  if (S.kind != STAGE_CONV || !any_ok(S, dtype) || S.cin % (16 / esz) == 0) return false;
+  const int wide = S.cout > 32 ? 64 : 32;
+  const int64_t large = pixel_blocks(S, 16, 16) * ((S.cout + wide - 1) / wide);
+  const bool small = static_cast<double>(large) * batch * share < 512.0;
+  const struct { int b, bn; } order[] = {{small ? 8 : 16, wide}, {8, wide}, {8, 32}};
+  for (const auto& o : order)
+    if (thin_layout(o.b, o.b, o.bn, S.f, S.s, S.cin, esz).total <= kThinLds) {
+      c->br = c->bc = o.b;
+      c->bn = o.bn;
+      c->bm = o.b * o.b;
+      c->blocks = pixel_blocks(S, o.b, o.b) * ((S.cout + o.bn - 1) / o.bn);
+      return true;
+    }
+  return false;
+}
+
 // Block shape and K groups of the any-filter kernel, from a model of one
 // compute unit fitted to a sweep of eleven layers (7x7/2 to 1x1/2, both data
 // types, 18x16 to 224x200; within 15 % of most points): a workgroup costs
@@ -280,12 +302,17 @@ StageConfig choose_config(const Stage& S, int batch, int dtype, double share) {
     return c;
   }
   if (!mfma_ok(S, dtype)) {
-    c.kind = rgb_ok(S) ? K_CONV_RGB : any_ok(S, dtype) ? K_CONV_ANY : K_CONV_DIRECT;
-    if (c.kind == K_CONV_ANY) choose_any(S, batch, dtype, &c);
-    // bf16 first layer with 16/32/64 outputs: K = 27 padded to one MFMA K.
-    if (c.kind == K_CONV_RGB && dtype == MAFAT_BF16 && (S.cout == 16 || S.cout == 32 || S.cout == 64)) {
+    if (rgb_ok(S) && dtype == MAFAT_BF16 && S.cout >= 16) {
+      // bf16 first layer with 16/32/64 outputs: K = 27 padded to one MFMA K.
       c.kind = K_CONV_RGB_MFMA;
       c.bn = S.cout;
+    } else if (choose_thin(S, batch, dtype, share, &c)) {
+      c.kind = K_CONV_THIN;
+    } else if (any_ok(S, dtype)) {
+      c.kind = K_CONV_ANY;
+      choose_any(S, batch, dtype, &c);
+    } else {
+      c.kind = K_CONV_DIRECT;
     }
     return tune_override(S, c);
   }
@@ -497,9 +524,9 @@ StageConfig stage_config(const mafat_plan& P, const Group& G, const Stage& S, in
   const int64_t src_frame = (S.src_buf == BUF_GROUP_IO) ? static_cast<int64_t>(din[0]) * din[1] * din[2]
                                                         : G.scratch_frame;
   if ((c.kind == K_CONV_MFMA || c.kind == K_CONV_RING || c.kind == K_CONV_PATCH || c.kind == K_CONV_ANY ||
-       c.kind == K_CONV_SPLIT) &&
+       c.kind == K_CONV_SPLIT || c.kind == K_CONV_THIN) &&
       src_frame * esz >= (1ll << 31))
-    c.kind = K_CONV_DIRECT;
+    c.kind = (c.kind == K_CONV_THIN && rgb_ok(S)) ? K_CONV_RGB : K_CONV_DIRECT;
   return c;
 }
 
@@ -816,7 +843,7 @@ int run_group_impl(const mafat_plan* plan, int g, int s_begin, int s_end, int ba
       const Stage& SC = first ? *S2 : S;  // the convolution whose GEMM the launch computes
       const int kind = cfg.kind;
       const bool matrix = (kind == K_CONV_MFMA || kind == K_CONV_RING || kind == K_CONV_PATCH || kind == K_CONV_ANY ||
-                          kind == K_CONV_SPLIT);
+                          kind == K_CONV_SPLIT || kind == K_CONV_THIN);
       const MfmaShape shape{cfg.bm, cfg.bn, cfg.depth, cfg.kg, cfg.wgm, cfg.wgn, cfg.kord, cfg.br, cfg.bc};
       const int bu = (kind == K_CONV_RGB) ? 256 / (S.cout / 8) : block_units(kind, shape);
       StageArgs A;
@@ -889,7 +916,7 @@ int run_group_impl(const mafat_plan* plan, int g, int s_begin, int s_end, int ba
           if (kind == K_CONV_RGB_MFMA)  // 2-D blocks of conv outputs
             total += static_cast<int64_t>((TC.ch + kRgbBlockRows - 1) / kRgbBlockRows) *
                      ((TC.cw + kRgbBlockCols - 1) / kRgbBlockCols);
-          else if (kind == K_CONV_PATCH || kind == K_CONV_SPLIT)
+          else if (kind == K_CONV_PATCH || kind == K_CONV_SPLIT || kind == K_CONV_THIN)
             total += static_cast<int64_t>((TC.ch + shape.br - 1) / shape.br) * ((TC.cw + shape.bc - 1) / shape.bc);
           else
             total += (units + bu - 1) / bu;
@@ -944,6 +971,8 @@ int run_group_impl(const mafat_plan* plan, int g, int s_begin, int s_end, int ba
           e = launch_conv_patch(S.pool, shape, A, stream, lev);
         } else if (kind == K_CONV_SPLIT) {
           e = launch_conv_split(S.pool, shape, A, stream, lev);
+        } else if (kind == K_CONV_THIN) {
+          e = launch_conv_thin(dtype, S.pool, shape, A, stream, lev);
         } else if (kind == K_CONV_ANY) {
           e = launch_conv_any(dtype, S.pool, shape, A, stream, lev);
         } else {
@@ -1117,6 +1146,7 @@ extern "C" int mafat_plan_stage_kernel(const mafat_plan* plan, int32_t group, in
       case K_CONV_RING: *kernel = MAFAT_KERNEL_RING; break;
       case K_CONV_SPLIT:
       case K_CONV_MFMA: *kernel = MAFAT_KERNEL_MFMA_F32; break;
+      case K_CONV_THIN: *kernel = rgb_ok(G.stages[stage]) ? MAFAT_KERNEL_FIRST_LAYER : MAFAT_KERNEL_GENERIC; break;
       case K_CONV_RGB:
       case K_CONV_RGB_MFMA: *kernel = MAFAT_KERNEL_FIRST_LAYER; break;
       case K_POOL: *kernel = MAFAT_KERNEL_POOL; break;
