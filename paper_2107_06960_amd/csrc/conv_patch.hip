@@ -109,7 +109,11 @@ __device__ __forceinline__ void pwait_stage(int rem) {
     }
   }
 }
+// The barrier alone: for slots that LDS DMA fills (pwait_vmcnt first) and that
+// are only read, their reads having been waited for by the MFMAs that use them.
 __device__ __forceinline__ void pbarrier() { asm volatile("s_barrier" ::: "memory"); }
+// After LDS writes of this wave that other waves read: they have to land first.
+__device__ __forceinline__ void pbarrier_writes() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // N2 > 0: a 1x1 convolution with N2 outputs of this stage's output (all BN
 // = c_out channels in the block) follows in the same workgroup: the block's
@@ -594,7 +598,9 @@ void conv_patch_kernel(const StageArgs a) {
     else
       first_layer(std::false_type{});
     MAFAT_PTRACE(7);
-    pbarrier();  // every wave is done with the input patch: taps 5-8 load over it
+    // The pooled values every wave has written are in the patch, and every wave
+    // is done with the input patch: taps 5-8 load over it.
+    pbarrier_writes();
 #pragma unroll
     for (int k = 0; k < NBW; ++k) {
       const int g = k * NWAVE + wave;
