@@ -173,6 +173,29 @@ void choose_any(const Stage& S, int batch, int dtype, StageConfig* c) {
   }
 }
 
+// The float32 1x1 layers (and the 3x3 ones whose channels are no whole
+// 32-channel chunks) of launches small enough that 32x32 blocks leave no
+// compute unit two workgroups: the any-filter kernel's K groups shorten the
+// chain of K steps that bounds them.  Two groups take ~0.53 us per 256 bytes
+// of K, four ~1.0 us per 512 (their workgroup is the unit's only one), the
+// 128-byte steps of conv_mfma_kernel 0.45 us each: 1x1 512->256 on nine 9x9
+// tiles 10.3 -> 7.1 us, 3x3 80->96 on 30x30 14.2 -> 8.6 us, 3x3 16->32 on
+// 32x32 5.7 -> 4.5 us; larger launches are as fast or faster with
+// conv_mfma_kernel (1x1 256->128 on nine 24x24 tiles 8.7 against 9.2 us).
+// Never fewer groups than there: more of them only shorten the sums.
+// For all of a stage's tiles: tile batches have to give the same bits.
+bool small_any(const Stage& S, int batch, StageConfig* c) {
+  int64_t mb = 0;
+  for (const TileGeom& T : S.tiles) mb += (static_cast<int64_t>(T.ch) * T.cw + 31) / 32;
+  const int64_t blocks = mb * ((S.cout + 31) / 32);
+  if (blocks * batch > 256) return false;
+  const int64_t pieces = static_cast<int64_t>(S.f) * S.f * S.cin / 4;
+  c->bm = c->bn = 32;
+  c->kg = (pieces + 31) / 32 * 100 < (pieces + 15) / 16 * 53 ? 4 : 2;
+  c->blocks = blocks;
+  return true;
+}
+
 // Block shape of the bf16 3x3 patch kernel, by a model fitted to a sweep of
 // sixty layers (YOLOv2's 3x3 stages at 608x608 under six tilings and batches,
 // a VGG-style stack, layers of 13x13 to 304x304 with 32 to 512 channels;
@@ -335,6 +358,14 @@ StageConfig choose_config(const Stage& S, int batch, int dtype, double share) {
     if (S.f == 1) {
       c.bm = (S.cin >= 256 && S.cout >= 64) ? 32 : 64;
       c.bn = (S.cout >= 64) ? 64 : 32;
+      // With three workgroups of 64 pixels for every compute unit the larger
+      // block's halved weight traffic counts more than the chain of its steps
+      // (256->128 on 76x76, eight frames: 14.8 us with 32, 14.0 us with 64).
+      if (c.bm == 32) {
+        int64_t mb64 = 0;
+        for (const TileGeom& T : S.tiles) mb64 += (static_cast<int64_t>(T.ch) * T.cw + 63) / 64;
+        if (static_cast<double>(mb64 * ((S.cout + 63) / 64)) * batch * share >= 3 * 256.0) c.bm = 64;
+      }
     } else if (S.cout >= 256) {
       c.bm = 128; c.bn = 64; c.kg = 2; c.depth = 4;
     } else if (S.cout >= 128) {
@@ -348,6 +379,8 @@ StageConfig choose_config(const Stage& S, int batch, int dtype, double share) {
   } else if (dtype != MAFAT_BF16 && S.f == 3 && S.cin % 32 == 0) {
     c.kind = K_CONV_SPLIT;
     choose_split(S, batch, share, &c);
+  } else if (dtype != MAFAT_BF16 && small_any(S, batch, &c)) {
+    c.kind = K_CONV_ANY;
   } else if (dtype != MAFAT_BF16) {
     c.kind = K_CONV_MFMA;
     const double clk = 2.4e9, mfma_rate = 4096.0 * clk, l2_rate = 64.0 * clk, t0 = 2e-6;
@@ -585,6 +618,9 @@ std::shared_ptr<const GroupRun> group_run(const mafat_plan& P, int group, int ba
     R->pack.push_back(P.packed_weights && c.kind == K_CONV_PATCH ? stage_pack_block(S, c) : 0);
   }
   if (G.reuse) R->bands = band_layout(P, G, dtype);
+#ifdef MAFAT_TUNING
+  return R;  // the override may change from run to run
+#endif
   const std::lock_guard<std::mutex> lock(P.run_mutex);
   if (P.runs.size() >= kKept) P.runs.erase(P.runs.begin());
   P.runs.emplace_back(mafat_plan::RunKey{group, batch, dtype}, R);
@@ -1144,6 +1180,7 @@ extern "C" int mafat_plan_stage_kernel(const mafat_plan* plan, int32_t group, in
     switch (c.kind) {
       case K_CONV_PATCH: *kernel = MAFAT_KERNEL_PATCH; break;
       case K_CONV_RING: *kernel = MAFAT_KERNEL_RING; break;
+      case K_CONV_ANY: *kernel = mfma_ok(G.stages[stage], dtype) ? MAFAT_KERNEL_MFMA_F32 : MAFAT_KERNEL_GENERIC; break;
       case K_CONV_SPLIT:
       case K_CONV_MFMA: *kernel = MAFAT_KERNEL_MFMA_F32; break;
       case K_CONV_THIN: *kernel = rgb_ok(G.stages[stage]) ? MAFAT_KERNEL_FIRST_LAYER : MAFAT_KERNEL_GENERIC; break;
