@@ -99,11 +99,10 @@ constexpr int kRgbBlockRows = 16, kRgbBlockCols = 32;
 // the number of K groups (1: 4 waves; 2: 8 waves, each group of 4 multiplies
 // one 64-byte half of every stage).
 // For the LDS-ring kernel, depth is the number of ring slots, wgm x wgn
-// the wave arrangement of one K group and kord the K order (0: tap-major,
-// 1: channel-block-major).
+// the wave arrangement.
 struct MfmaShape {
   int bm, bn, depth, kg;
-  int wgm, wgn, kord;
+  int wgm, wgn;
   int br, bc;  // patch kernel: block of br x bc conv outputs (bm >= br * bc GEMM rows)
 };
 
@@ -138,20 +137,20 @@ struct MfmaShape {
 #define MAFAT_PATCH_TUNE_SHAPES
 #endif
 
-// Instantiated LDS-ring kernel shapes: (bm, bn, wgm, wgn, kg, ring slots, K order).
-#define MAFAT_RING_SHAPES             \
-  MAFAT_RING(32, 64, 2, 2, 1, 3, 1)   \
-  MAFAT_RING(64, 32, 2, 2, 1, 3, 1)   \
-  MAFAT_RING(64, 64, 2, 2, 1, 3, 1)   \
-  MAFAT_RING(128, 64, 2, 2, 2, 4, 1)  \
-  MAFAT_RING(128, 128, 2, 2, 2, 3, 1)
+// Instantiated LDS-ring kernel shapes: (bm, bn, wgm, wgn, ring slots).
+#define MAFAT_RING_SHAPES       \
+  MAFAT_RING(32, 64, 2, 2, 3)   \
+  MAFAT_RING(64, 32, 2, 2, 3)   \
+  MAFAT_RING(64, 64, 2, 2, 3)
 #ifdef MAFAT_TUNING
-#define MAFAT_RING_TUNE_SHAPES        \
-  MAFAT_RING(32, 64, 2, 2, 1, 6, 1)   \
-  MAFAT_RING(32, 64, 2, 2, 1, 8, 1)   \
-  MAFAT_RING(32, 32, 2, 2, 1, 3, 1)   \
-  MAFAT_RING(32, 32, 2, 2, 1, 4, 1)   \
-  MAFAT_RING(64, 64, 2, 2, 2, 4, 1)
+#define MAFAT_RING_TUNE_SHAPES  \
+  MAFAT_RING(32, 64, 2, 2, 6)   \
+  MAFAT_RING(32, 64, 2, 2, 8)   \
+  MAFAT_RING(64, 64, 2, 2, 4)   \
+  MAFAT_RING(64, 64, 2, 2, 6)   \
+  MAFAT_RING(32, 64, 2, 2, 4)   \
+  MAFAT_RING(32, 32, 2, 2, 3)   \
+  MAFAT_RING(32, 32, 2, 2, 4)
 #else
 #define MAFAT_RING_TUNE_SHAPES
 #endif
@@ -208,7 +207,7 @@ hipError_t launch_stage(int kind, int dtype, int f, bool pool, MfmaShape shape,
                         const StageArgs& args, hipStream_t stream, LaunchEvents ev);
 
 // Launch one bf16 LDS-ring convolution stage chunk (conv_ring.hip).
-hipError_t launch_conv_ring(int f, bool pool, const MfmaShape& shape, const StageArgs& args,
+hipError_t launch_conv_ring(bool pool, const MfmaShape& shape, const StageArgs& args,
                             hipStream_t stream, LaunchEvents ev);
 
 // Launch one float32 3x3 split-operand stage chunk (conv_split.hip).

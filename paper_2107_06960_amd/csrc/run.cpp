@@ -73,7 +73,7 @@ bool any_ok(const Stage& S, int dtype) {
   return S.kind == STAGE_CONV && static_cast<int64_t>(S.cout) * S.f * S.f * S.cin * esz < (1ll << 31);
 }
 
-// Tuning builds only: MAFAT_TUNE="first_layer:bm,bn,depth[,chan_major[,kg[,kind[,kord[,br,bc[,wgm,wgn]]]]]];..."
+// Tuning builds only: MAFAT_TUNE="first_layer:bm,bn,depth[,chan_major[,kg[,kind[,0[,br,bc[,wgm,wgn]]]]]];..."
 // forces the configuration of the stage starting at first_layer (kind: 0 the
 // register-staged matrix-core kernel, 5 the LDS-ring kernel, 6 the 3x3 patch
 // kernel).
@@ -93,7 +93,6 @@ StageConfig tune_override(const Stage& S, StageConfig c) {
         if (cm >= 0) c.chan_major = cm;
         if (kg >= 1) c.kg = kg;
         if (kind >= 0) c.kind = kind;
-        if (ko >= 0) c.kord = ko;
         if (br > 0 && bc > 0) { c.br = br; c.bc = bc; }
         if (wgm > 0 && wgn > 0) { c.wgm = wgm; c.wgn = wgn; }
       }
@@ -345,33 +344,23 @@ StageConfig choose_config(const Stage& S, int batch, int dtype, double share) {
     c.kind = K_CONV_PATCH;
     choose_patch(S, batch, share, &c);
   }
-  if (dtype == MAFAT_BF16 && S.f != 3) {
-    // LDS-ring kernel.  Block shapes from a sweep over every YOLOv2 stage
-    // at 608x608 (tiling 5x5/8/2x2; blocks 32..128 x 32..128, ring depths
-    // 2..8, one or two K groups): the K loop of a workgroup is bound by LDS
-    // traffic and by the operand bytes it keeps in flight, so wide layers
-    // take large blocks with two K groups (8 waves), narrow ones small
-    // blocks with several workgroups per CU, and 1x1 layers with a long K
-    // the smallest block.
+  if (dtype == MAFAT_BF16 && S.f == 1) {
+    // LDS-ring kernel.  Block shapes from a sweep over the YOLOv2 stages at
+    // 608x608 (tiling 5x5/8/2x2): layers with a long K take the smallest
+    // block, whose workgroups fill the chip.
     c.kind = K_CONV_RING;
-    c.depth = 3; c.kg = 1; c.kord = 1;
-    if (S.f == 1) {
-      c.bm = (S.cin >= 256 && S.cout >= 64) ? 32 : 64;
-      c.bn = (S.cout >= 64) ? 64 : 32;
-      // With three workgroups of 64 pixels for every compute unit the larger
-      // block's halved weight traffic counts more than the chain of its steps
-      // (256->128 on 76x76, eight frames: 14.8 us with 32, 14.0 us with 64).
-      if (c.bm == 32) {
-        int64_t mb64 = 0;
-        for (const TileGeom& T : S.tiles) mb64 += (static_cast<int64_t>(T.ch) * T.cw + 63) / 64;
-        if (static_cast<double>(mb64 * ((S.cout + 63) / 64)) * batch * share >= 3 * 256.0) c.bm = 64;
-      }
-    } else if (S.cout >= 256) {
-      c.bm = 128; c.bn = 64; c.kg = 2; c.depth = 4;
-    } else if (S.cout >= 128) {
-      c.bm = 128; c.bn = 128; c.kg = 2; c.depth = 3;
-    } else {
-      c.bm = 64; c.bn = (S.cout >= 64) ? 64 : 32;
+    c.depth = 3; c.kg = 1;
+    c.bm = (S.cin >= 256 && S.cout >= 64) ? 32 : 64;
+    c.bn = (S.cout >= 64) ? 64 : 32;
+    // With two workgroups of 64 pixels for every compute unit the larger
+    // block's halved weight traffic counts more than the chain of its steps:
+    // 512->256 on 38x38, eight frames (736 blocks of 64): 10.8 us with 32,
+    // 8.3 us with 64; four frames (384): 6.7 with either; 256->128 on 76x76,
+    // four frames (736): 8.1 and 6.4 us, two frames (368): 5.2 and 5.3 us.
+    if (c.bm == 32) {
+      int64_t mb64 = 0;
+      for (const TileGeom& T : S.tiles) mb64 += (static_cast<int64_t>(T.ch) * T.cw + 63) / 64;
+      if (static_cast<double>(mb64 * ((S.cout + 63) / 64)) * batch * share >= 2 * 256.0) c.bm = 64;
     }
     int64_t mb = 0;
     for (const TileGeom& T : S.tiles) mb += (static_cast<int64_t>(T.ch) * T.cw + c.bm - 1) / c.bm;
@@ -494,7 +483,7 @@ StageConfig first_pair_config(const Stage& B, int batch, double share) {
       {8, 8, 64, 5.6, 2.0, 2.1}, {8, 16, 128, 6.5, 2.6, 1.67}, {12, 16, 192, 7.3, 3.4, 2.9}, {14, 18, 256, 8.3, 4.1, 4.5}};
   StageConfig c{};
   c.kind = K_CONV_PATCH;
-  c.bn = 64; c.wgm = 4; c.wgn = 2; c.depth = 1; c.kg = 1; c.kord = 1; c.chan_major = 0;
+  c.bn = 64; c.wgm = 4; c.wgn = 2; c.depth = 1; c.kg = 1; c.chan_major = 0;
   double best = 1e30;
   for (const FS& f : kShapes) {
     const int64_t mb = pixel_blocks(B, f.br, f.bc);
@@ -535,7 +524,7 @@ StageConfig stage_config(const mafat_plan& P, const Group& G, const Stage& S, in
     // tile takes 8.8 us with them and 7.2 us with the latter.
     StageConfig c{};
     c.kind = K_CONV_PATCH;
-    c.br = 8; c.bn = 128; c.wgm = 4; c.wgn = 2; c.depth = 1; c.kg = 1; c.kord = 1;
+    c.br = 8; c.bn = 128; c.wgm = 4; c.wgn = 2; c.depth = 1; c.kg = 1;
     double best = 1e30;
     for (const int bc : {16, 8}) {
       const int64_t mb = pixel_blocks(S, 8, bc);
@@ -880,7 +869,7 @@ int run_group_impl(const mafat_plan* plan, int g, int s_begin, int s_end, int ba
       const int kind = cfg.kind;
       const bool matrix = (kind == K_CONV_MFMA || kind == K_CONV_RING || kind == K_CONV_PATCH || kind == K_CONV_ANY ||
                           kind == K_CONV_SPLIT || kind == K_CONV_THIN);
-      const MfmaShape shape{cfg.bm, cfg.bn, cfg.depth, cfg.kg, cfg.wgm, cfg.wgn, cfg.kord, cfg.br, cfg.bc};
+      const MfmaShape shape{cfg.bm, cfg.bn, cfg.depth, cfg.kg, cfg.wgm, cfg.wgn, cfg.br, cfg.bc};
       const int bu = (kind == K_CONV_RGB) ? 256 / (S.cout / 8) : block_units(kind, shape);
       StageArgs A;
       std::memset(&A, 0, sizeof(A));
@@ -998,7 +987,7 @@ int run_group_impl(const mafat_plan* plan, int g, int s_begin, int s_end, int ba
         if (A.total_blocks <= 0) {
           e = hipSuccess;
         } else if (kind == K_CONV_RING) {
-          e = launch_conv_ring(S.f, S.pool, shape, A, stream, lev);
+          e = launch_conv_ring(S.pool, shape, A, stream, lev);
         } else if (first) {
           e = launch_conv_patch_first(shape, A, stream, lev);
         } else if (fuse) {
@@ -1195,12 +1184,12 @@ extern "C" int mafat_plan_stage_kernel(const mafat_plan* plan, int32_t group, in
 
 #ifdef MAFAT_TUNING
 // Tuning builds only: the configuration the runtime picks for stage s of
-// group g: kind, bm, bn, depth, kg, kord, br, bc.
+// group g: kind, bm, bn, depth, kg, 0, br, bc.
 extern "C" int mafat_debug_config(const mafat_plan* plan, int32_t g, int32_t s, int32_t batch, int32_t dtype,
                                   int32_t* out) {
   const mafat::Stage& S = plan->groups[g].stages[s];
   const mafat::StageConfig c = mafat::choose_config(S, batch, dtype, 1.0);
-  const int32_t v[8] = {c.kind, c.bm, c.bn, c.depth, c.kg, c.kord, c.br, c.bc};
+  const int32_t v[8] = {c.kind, c.bm, c.bn, c.depth, c.kg, 0, c.br, c.bc};
   for (int k = 0; k < 8; ++k) out[k] = v[k];
   return 0;
 }

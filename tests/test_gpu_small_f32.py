@@ -16,7 +16,9 @@ pytestmark = pytest.mark.gpu
 CASES = [("f32", 512, 256, 1, 26, 26, False, "3x3", 1), ("f32", 512, 256, 1, 26, 26, False, "3x3", 2),
          ("f32", 16, 32, 3, 32, 32, False, "2x2", 1), ("f32", 16, 32, 3, 100, 90, True, "2x2", 1),
          ("f32", 80, 96, 3, 30, 29, True, "2x2", 1), ("f32", 64, 16, 1, 9, 7, False, "1x1", 3),
-         ("bf16", 256, 128, 1, 76, 75, False, "2x2", 1), ("bf16", 256, 128, 1, 76, 75, False, "2x2", 5)]
+         ("bf16", 256, 128, 1, 76, 75, False, "2x2", 1), ("bf16", 256, 128, 1, 76, 75, False, "2x2", 5),
+         ("bf16", 480, 256, 1, 37, 38, False, "1x1", 6), ("bf16", 96, 48, 1, 41, 38, True, "2x1", 2),
+         ("bf16", 32, 32, 1, 9, 7, False, "1x1", 1)]
 
 
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "-".join(str(v) for v in c))
