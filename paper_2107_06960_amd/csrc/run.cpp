@@ -477,10 +477,14 @@ StageConfig first_pair_config(const Stage& B, int batch, double share) {
   // us for each of the next few, which share the unit, and `each` us for each
   // once it is full.  One 72x72 tile: 5.6 / 6.4 / 7.2 / 8.2 us with 64, 128,
   // 192 and 256 rows; twenty-five tiles at 608x608: 17.6 / 13.9 / 14.6 / 12.4
-  // us; with eight frames 100 / 69 / 69 / 74 us.
+  // us.  `each` is that of launches inside a whole network, where the smaller
+  // blocks' recomputed first layer costs more than in a loop of this launch
+  // alone: the 608x608 network with 5x5 tiles and eight frames takes 381 / 355
+  // / 356 / 342 us a pass, with 4x4 tiles down to layer 11 441 / 405 / 400 /
+  // 404 us (the launch alone, 5x5 tiles: 89 / 62 / 61 / 69 us).
   struct FS { int br, bc, bm; double one, more, each; };
   static const FS kShapes[] = {
-      {8, 8, 64, 5.6, 2.0, 2.1}, {8, 16, 128, 6.5, 2.6, 1.67}, {12, 16, 192, 7.3, 3.4, 2.9}, {14, 18, 256, 8.3, 4.1, 4.5}};
+      {8, 8, 64, 5.6, 2.0, 2.1}, {8, 16, 128, 6.5, 2.6, 2.7}, {12, 16, 192, 7.3, 3.4, 3.8}, {14, 18, 256, 8.3, 4.1, 4.6}};
   StageConfig c{};
   c.kind = K_CONV_PATCH;
   c.bn = 64; c.wgm = 4; c.wgn = 2; c.depth = 1; c.kg = 1; c.chan_major = 0;
