@@ -1,19 +1,20 @@
 // conv_split.hip -- float32 3x3 convolution stage (stride 1, zero padding
 // outside the image, folded batch-norm scale/bias, activation, optional fused
 // 2x2/2 max-pool) on the bf16 matrix cores: every float32 operand is split
-// exactly into three bf16 parts, x = x0 + x1 + x2 (8 significant bits each, by
-// truncation), and a product is the sum of the six part products that reach
-// above 2^-24 of it: x0 w0, x0 w1, x1 w0, x1 w1, x0 w2, x2 w0, each exact in
-// float32.
+// exactly into three bf16 parts, x = x0 + x1 + x2 (8 significant bits each,
+// each part the nearest to what is left), and a product is the sum of six part
+// products: x0 w0, x0 w1, x1 w0, x1 w1, x0 w2, x2 w0, each exact in float32.
 //
 // Why: the fp32 MFMA runs at 1/16 of the bf16 rate (157 against 2517 TFLOP/s
 // dense), so six bf16 MFMAs take 3/8 of the time of the fp32 ones they
 // replace.  Precision: x0 w0 is summed in one accumulator (one rounding per
 // 32 products instead of one per product), the five small terms in another,
-// added at the end; against 64-bit sums the relative error is 2.2e-7 where
-// the fp32 MFMA chain's is 6.0e-7 (K = 1152, leaky activations; 1.1e-7 against
-// 3.0e-7 at K = 288, 4.4e-7 against 1.2e-6 at K = 4608).  The dropped terms
-// (x1 w2, x2 w1, x2 w2) are below 2^-24 of a product.
+// added at the end.  Dropped are x1 w2, x2 w1 and x2 w2: |x1| <= 2^-8 |x| and
+// |x2| <= 2^-17 |x|, so they are at most 2^-24 (1 + 2^-9) of a product, of
+// either sign (rms 5.5e-9 of a product); parts cut off instead of rounded
+// would drop up to 2^-21, always towards zero.  YOLOv2's first 16 layers at
+// 416x416 against 64-bit sums: 7.5e-7 (parts cut off 8.1e-7, the fp32 MFMA
+// chain 1.7e-6).
 //
 // What the split cannot carry: infinities and NaN (their parts are not sums),
 // sums past the largest float, and operands so small that parts fall below
@@ -49,20 +50,29 @@ namespace {
 // into registers stay in flight).
 __device__ __forceinline__ void split_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-// Eight floats -> their three bf16 parts, packed.
+// Two floats to the nearest bf16 (ties to even), packed; and its two values.
+__device__ __forceinline__ unsigned near2(float a, float b) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2{a, b}), bf16x2));
+}
+__device__ __forceinline__ float lo_of(unsigned p) { return __uint_as_float(p << 16); }
+__device__ __forceinline__ float hi_of(unsigned p) { return __uint_as_float(p & 0xffff0000u); }
+
+// Eight floats -> their three bf16 parts, packed: each part the bf16 nearest to
+// what the ones before it leave.  That rest is exact in float32, and the third
+// part holds all of the last one.
 __device__ __forceinline__ void split8(const u32x4& lo, const u32x4& hi, u32x4 (&out)[3]) {
 #pragma unroll
   for (int w = 0; w < 4; ++w) {
-    const unsigned a = w < 2 ? lo[2 * w] : hi[2 * w - 4], b = w < 2 ? lo[2 * w + 1] : hi[2 * w - 3];
-    const float ra = __uint_as_float(a) - __uint_as_float(a & 0xffff0000u);
-    const float rb = __uint_as_float(b) - __uint_as_float(b & 0xffff0000u);
-    const unsigned ua = __float_as_uint(ra), ub = __float_as_uint(rb);
-    const float sa = ra - __uint_as_float(ua & 0xffff0000u);
-    const float sb = rb - __uint_as_float(ub & 0xffff0000u);
-    // the upper halves of two words in one
-    out[0][w] = __builtin_amdgcn_perm(b, a, 0x07060302u);
-    out[1][w] = __builtin_amdgcn_perm(ub, ua, 0x07060302u);
-    out[2][w] = __builtin_amdgcn_perm(__float_as_uint(sb), __float_as_uint(sa), 0x07060302u);
+    const float a = __uint_as_float(w < 2 ? lo[2 * w] : hi[2 * w - 4]);
+    const float b = __uint_as_float(w < 2 ? lo[2 * w + 1] : hi[2 * w - 3]);
+    const unsigned p0 = near2(a, b);
+    const float ra = a - lo_of(p0), rb = b - hi_of(p0);
+    const unsigned p1 = near2(ra, rb);
+    out[0][w] = p0;
+    out[1][w] = p1;
+    out[2][w] = near2(ra - lo_of(p1), rb - hi_of(p1));
   }
 }
 

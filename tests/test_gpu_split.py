@@ -3,8 +3,12 @@
 Finite data against the oracle: blocks that are cut off on every side, output
 channels that fill no block, one and several chunks, the fused pool, batches
 and every execution of a plan.  The tolerance is that of plain float32: sums of
-K products of which each is off by at most 2^-24 and rounded at most K times,
-so max|gpu - oracle| <= 4 sqrt(K) 2^-24 max|sum| for independent roundings.
+K products of which each is off by at most 2^-24 (what the dropped part products
+hold, of either sign) and rounded at most K times, so
+max|gpu - oracle| <= 4 sqrt(K) 2^-24 max|sum| for independent roundings.
+
+Single products and sums of equal ones against float64: the error of a product
+shows there, where a dense sum's roundings hide it.
 
 Data the split cannot carry (infinities, NaN, sums past the largest float,
 operands whose parts fall below the smallest bf16) against the same sums in
@@ -38,6 +42,47 @@ def test_split_conv(orc, case):
     for kw in ({}, {"part": True}, {"reuse": True}):
         out = run_gpu(layers, h, w, cin, par, tiling, batch, "f32", want_cuts=False, **kw)
         assert normwise_err(out, ref) <= 4 * np.sqrt(9 * cin) * 2.0 ** -24, kw
+
+
+def _center_sums(x, w, terms):
+    """conv outputs (linear, unit scale, no bias) of x (pixels) times w (channels), the same pair in the first `terms`
+    channels of the centre tap and zeros elsewhere, as (pixels, channels)."""
+    import torch
+    from paper_2107_06960_amd import mafat as M
+    n, cout, cin = len(x), len(w), 32
+    par = {"w": [np.zeros((cout, 3, 3, cin), np.float32)], "scale": [np.ones(cout, np.float32)],
+           "bias": [np.zeros(cout, np.float32)]}
+    par["w"][0][:, 1, 1, :terms] = w[:, None]
+    xt = np.zeros((1, n // 32, 32, cin), np.float32)
+    xt[..., :terms] = x.reshape(1, n // 32, 32, 1)
+    net = M.Network(M.Plan([W.conv(cout, act=W.LINEAR)], (n // 32, 32, cin), "1x1"), par, 1, "f32")
+    return net.run(torch.from_numpy(xt).cuda()).double().cpu().numpy().reshape(n, cout)
+
+
+def test_split_single_products():
+    # A sum of one term is off by its final rounding (at most 2^-24, rms 0.74 / sqrt(3) 2^-24 = 2.5e-8 over
+    # mantissas spread evenly in their logarithm), the rounding of the five small terms (at most 2^-30) and the dropped ones (at
+    # most 2^-24, rms 5.5e-9): 2^-23 and 2^-25 in all.
+    require_gpu()
+    rng = np.random.default_rng(19)
+    x, w = rng.standard_normal(4096).astype(np.float32), rng.standard_normal(64).astype(np.float32)
+    print("[split] single products", flush=True)
+    ref = x.astype(np.float64)[:, None] * w.astype(np.float64)[None]
+    err = _center_sums(x, w, 1) / ref - 1.0
+    assert np.max(np.abs(err)) <= 2.0 ** -23
+    assert np.sqrt(np.mean(err ** 2)) <= 2.0 ** -25
+
+
+# the largest dropped terms of parts cut off, and of parts rounded to nearest (the second part just below a tie)
+@pytest.mark.parametrize("units", [2 ** 16 - 1, 32703, -32703, 2 ** 15, 3 * 2 ** 14 + 1])
+def test_split_equal_products(units):
+    # 32 equal products: dropped terms that do not average out (2^-24), one rounding of the sum of the first parts' products, one
+    # of the small ones' (2^-32), one of the end: 3 * 2^-24.
+    require_gpu()
+    v = np.float32(1.0 + units * 2.0 ** -23)
+    print(f"[split] 32 times ({float(v)!r})^2", flush=True)
+    out = _center_sums(np.full(32, v, np.float32), np.full(32, v, np.float32), 32)
+    assert np.max(np.abs(out / (32 * float(v) ** 2) - 1.0)) <= 3 * 2.0 ** -24
 
 
 def _conv64(x, par, pool):
