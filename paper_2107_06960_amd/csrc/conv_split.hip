@@ -1,9 +1,10 @@
 // conv_split.hip -- float32 3x3 convolution stage (stride 1, zero padding
 // outside the image, folded batch-norm scale/bias, activation, optional fused
 // 2x2/2 max-pool) on the bf16 matrix cores: every float32 operand is split
-// exactly into three bf16 parts, x = x0 + x1 + x2 (8 significant bits each,
-// each part the nearest to what is left), and a product is the sum of six part
-// products: x0 w0, x0 w1, x1 w0, x1 w1, x0 w2, x2 w0, each exact in float32.
+// exactly into three bf16 parts, 2^24 x = x0 + x1 + x2 (8 significant bits
+// each, each part the nearest to what is left), and a product is the sum of six
+// part products: x0 w0, x0 w1, x1 w0, x1 w1, x0 w2, x2 w0, each exact in
+// float32.
 //
 // Why: the fp32 MFMA runs at 1/16 of the bf16 rate (157 against 2517 TFLOP/s
 // dense), so six bf16 MFMAs take 3/8 of the time of the fp32 ones they
@@ -12,15 +13,18 @@
 // added at the end.  Dropped are x1 w2, x2 w1 and x2 w2: |x1| <= 2^-8 |x| and
 // |x2| <= 2^-17 |x|, so they are at most 2^-24 (1 + 2^-9) of a product, of
 // either sign (rms 5.5e-9 of a product); parts cut off instead of rounded
-// would drop up to 2^-21, always towards zero.  YOLOv2's first 16 layers at
-// 416x416 against 64-bit sums: 7.5e-7 (parts cut off 8.1e-7, the fp32 MFMA
-// chain 1.7e-6).
+// would drop up to 2^-21, always towards zero.  The factor 2^24 keeps the parts
+// of every float32, the smallest subnormal's too, clear of the bf16 subnormals:
+// without it parts fall below the smallest bf16 from operands of 2^-110 down.
+// Relative error of a layer against 64-bit sums (leaky activations), K = 288,
+// 1152 and 4608: 1.1e-7, 2.1e-7 and 4.1e-7 (the fp32 MFMA chain 2.9e-7, 5.9e-7
+// and 1.2e-6).  The factor costs one multiplication a value: 0.5 to 1.5 % of the
+// time of float32 networks.
 //
 // What the split cannot carry: infinities and NaN (their parts are not sums),
-// sums past the largest float, and operands so small that parts fall below
-// the smallest bf16.  A block whose accumulators hold anything not finite, or
-// whose largest one is below 2^-80 without being zero, is computed again on
-// the vector ALUs in plain float32 before it is stored.
+// operands from 2^104 and sums of products from 2^80 up (2^48 times that is
+// past the largest float).  A wave whose accumulators hold anything not finite
+// is computed again on the vector ALUs in plain float32 before it is stored.
 //
 // Structure: a workgroup owns a BR x BC block of conv outputs of one tile and
 // BN output channels.  K runs over 32-channel chunks and, in each, the three
@@ -29,10 +33,10 @@
 // (the layout of conv_patch.hip), and per step the three taps' BN weight rows
 // likewise; both are double buffered.  The float32 values come through
 // registers (two 16-byte loads per 8 channels), issued two steps ahead, are
-// split (5.5 vector instructions per value) and written after the MFMAs of
+// split (6.5 vector instructions per value) and written after the MFMAs of
 // the step before theirs: the split of one wave runs while the other wave of
 // its SIMD has the matrix core.  Per step and 128 x 64 block: 2304 matrix-core
-// cycles per compute unit, ~700 vector cycles, 336 KiB of LDS traffic.
+// cycles per compute unit, ~830 vector cycles, 336 KiB of LDS traffic.
 // Measured: see choose_split in run.cpp.
 //
 // Requires f = 3, c_in % 32 == 0, c_out % 16 == 0, byte offsets below 2^31
@@ -59,14 +63,15 @@ __device__ __forceinline__ unsigned near2(float a, float b) {
 __device__ __forceinline__ float lo_of(unsigned p) { return __uint_as_float(p << 16); }
 __device__ __forceinline__ float hi_of(unsigned p) { return __uint_as_float(p & 0xffff0000u); }
 
-// Eight floats -> their three bf16 parts, packed: each part the bf16 nearest to
-// what the ones before it leave.  That rest is exact in float32, and the third
-// part holds all of the last one.
+// Eight floats -> the three bf16 parts of kSplitScale times them, packed: each
+// part the bf16 nearest to what the ones before it leave.  That rest is exact in
+// float32, and the third part holds all of the last one.
+constexpr float kSplitScale = 0x1p24f;
 __device__ __forceinline__ void split8(const u32x4& lo, const u32x4& hi, u32x4 (&out)[3]) {
 #pragma unroll
   for (int w = 0; w < 4; ++w) {
-    const float a = __uint_as_float(w < 2 ? lo[2 * w] : hi[2 * w - 4]);
-    const float b = __uint_as_float(w < 2 ? lo[2 * w + 1] : hi[2 * w - 3]);
+    const float a = kSplitScale * __uint_as_float(w < 2 ? lo[2 * w] : hi[2 * w - 4]);
+    const float b = kSplitScale * __uint_as_float(w < 2 ? lo[2 * w + 1] : hi[2 * w - 3]);
     const unsigned p0 = near2(a, b);
     const float ra = a - lo_of(p0), rb = b - hi_of(p0);
     const unsigned p1 = near2(ra, rb);
@@ -327,22 +332,17 @@ __global__ __launch_bounds__(64 * WGM * WGN) void conv_split_kernel(const StageA
     const int oy = POOL ? (by0 + *py) >> 1 : by0 + *py, ox = POOL ? (bx0 + *px) >> 1 : bx0 + *px;
     return ((oy - tl.dy0) * tl.dw + (ox - tl.dx0)) * cout;
   };
-  bool bad = false, big = false, some = false;
+  bool bad = false;
 #pragma unroll
   for (int j = 0; j < NT; ++j)
 #pragma unroll
     for (int i = 0; i < MT; ++i)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        acc[j][i][r] += low[j][i][r];
-        const float m = fabsf(acc[j][i][r]);
-        bad = bad || !(m <= 3.4028234663852886e38f);
-        big = big || m >= 0x1p-80f;
-        some = some || m > 0.f;
+        acc[j][i][r] = (acc[j][i][r] + low[j][i][r]) * (1.f / kSplitScale / kSplitScale);
+        bad = bad || !(fabsf(acc[j][i][r]) <= 3.4028234663852886e38f);
       }
-  const bool again = __builtin_amdgcn_ballot_w64(bad) != 0 ||
-                     (__builtin_amdgcn_ballot_w64(some) != 0 && __builtin_amdgcn_ballot_w64(big) == 0);
-  if (__builtin_expect(again, 0)) {
+  if (__builtin_expect(__builtin_amdgcn_ballot_w64(bad) != 0, 0)) {
     // What the split could not carry: this wave's outputs in plain float32.
     const float* wgt = static_cast<const float*>(a.w);
 #pragma unroll 1
@@ -355,16 +355,16 @@ __global__ __launch_bounds__(64 * WGM * WGN) void conv_split_kernel(const StageA
       float mx = 0.f;
 #pragma unroll 1
       for (int s = 0; s < (POOL ? 4 : 1); ++s) {
-        float sum = 0.f;
+        float one = 0.f;
 #pragma unroll 1
         for (int t = 0; t < 9; ++t) {
           const int iy = by0 + py + (s >> 1) + t / 3 - 1, ix = bx0 + px + (s & 1) + t % 3 - 1;
           const bool in = iy >= 0 && iy < a.in_h && ix >= 0 && ix < a.in_w;
           const float* xp = src + (in ? ((iy - tl.sy0) * tl.sw + (ix - tl.sx0)) * cin : 0);
           const float* wp = wgt + (static_cast<int64_t>(co) * 9 + t) * cin;
-          for (int ci = 0; ci < cin; ++ci) sum = fmaf(in ? xp[ci] : 0.f, wp[ci], sum);
+          for (int ci = 0; ci < cin; ++ci) one = fmaf(in ? xp[ci] : 0.f, wp[ci], one);
         }
-        const float v = fmaf(sum, a.scale[co], a.bias[co]);
+        const float v = fmaf(one, a.scale[co], a.bias[co]);
         mx = s == 0 ? v : fmaxf(mx, v);
       }
       dst[o + co] = fmaxf(mx, slope * mx);

@@ -10,9 +10,10 @@ max|gpu - oracle| <= 4 sqrt(K) 2^-24 max|sum| for independent roundings.
 Single products and sums of equal ones against float64: the error of a product
 shows there, where a dense sum's roundings hide it.
 
-Data the split cannot carry (infinities, NaN, sums past the largest float,
-operands whose parts fall below the smallest bf16) against the same sums in
-float64 on the CPU: the kernel computes such blocks again in plain float32."""
+Data the split cannot carry (infinities, NaN, sums past the largest float)
+against the same sums in float64 on the CPU: the kernel computes such outputs
+again in plain float32.  Operands down to subnormals are no such data: the
+parts are of 2^24 times the value."""
 import numpy as np
 import pytest
 
@@ -83,6 +84,23 @@ def test_split_equal_products(units):
     print(f"[split] 32 times ({float(v)!r})^2", flush=True)
     out = _center_sums(np.full(32, v, np.float32), np.full(32, v, np.float32), 32)
     assert np.max(np.abs(out / (32 * float(v) ** 2) - 1.0)) <= 3 * 2.0 ** -24
+
+
+# binary exponents of the inputs (of every other pixel's; the rest are near 1) and of the weights: parts as they are would fall
+# below the smallest bf16, beside sums of any size in the same wave
+@pytest.mark.parametrize("xe,we", [(-118, 0), (-118, 60), (-125, 30), (-140, 100), (60, -118), (90, -140)])
+def test_split_small_operands(xe, we):
+    # as for single products: 2^-23
+    require_gpu()
+    rng = np.random.default_rng(29)
+    print(f"[split] inputs 2^{xe}, weights 2^{we}", flush=True)
+    x = np.where(np.arange(4096) % 2 == 0, 2.0 ** xe, 1.0) * rng.uniform(1, 2, 4096) * rng.choice([-1, 1], 4096)
+    x, w = x.astype(np.float32), (2.0 ** we * rng.uniform(1, 2, 64)).astype(np.float32)
+    ref = x.astype(np.float64)[:, None] * w.astype(np.float64)[None]
+    ok = np.abs(ref) >= 2.0 ** -126  # normal results
+    assert ok[::2].mean() == 1.0 or we == 0
+    err = _center_sums(x, w, 1)[ok] / ref[ok] - 1.0
+    assert np.max(np.abs(err)) <= 2.0 ** -23
 
 
 def _conv64(x, par, pool):
