@@ -24,7 +24,11 @@
 // What the split cannot carry: infinities and NaN (their parts are not sums),
 // operands from 2^104 and sums of products from 2^80 up (2^48 times that is
 // past the largest float).  A wave whose accumulators hold anything not finite
-// is computed again on the vector ALUs in plain float32 before it is stored.
+// is computed again in plain float32, on the fp32 MFMA with its operands straight
+// from memory, before it is stored: one such pixel in an early layer reaches all
+// waves of the later ones, so their time has to stay that of a convolution.
+// 3x3 512->512 on 26x26 with a NaN in every window takes 156 us (60 without), and
+// 4984 us with one output after the other on the vector ALUs.
 //
 // Structure: a workgroup owns a BR x BC block of conv outputs of one tile and
 // BN output channels.  K runs over 32-channel chunks and, in each, the three
@@ -343,55 +347,81 @@ __global__ __launch_bounds__(64 * WGM * WGN) void conv_split_kernel(const StageA
         bad = bad || !(fabsf(acc[j][i][r]) <= 3.4028234663852886e38f);
       }
   if (__builtin_expect(__builtin_amdgcn_ballot_w64(bad) != 0, 0)) {
-    // What the split could not carry: this wave's outputs in plain float32.
-    const float* wgt = static_cast<const float*>(a.w);
-#pragma unroll 1
-    for (int e = 0; e < MT * NT * (POOL ? 1 : 4); ++e) {
-      const int i = e % MT, j = e / MT % NT, k = e / (MT * NT);
-      const int co = n0 + wn * WN + j * 16 + (POOL ? (lane & 15) : 4 * (lane >> 4) + k);
-      int py, px;
-      const int o = row_out(i, &py, &px);
-      if (o < 0 || co >= cout) continue;
-      float mx = 0.f;
-#pragma unroll 1
-      for (int s = 0; s < (POOL ? 4 : 1); ++s) {
-        float one = 0.f;
-#pragma unroll 1
-        for (int t = 0; t < 9; ++t) {
-          const int iy = by0 + py + (s >> 1) + t / 3 - 1, ix = bx0 + px + (s & 1) + t % 3 - 1;
-          const bool in = iy >= 0 && iy < a.in_h && ix >= 0 && ix < a.in_w;
-          const float* xp = src + (in ? ((iy - tl.sy0) * tl.sw + (ix - tl.sx0)) * cin : 0);
-          const float* wp = wgt + (static_cast<int64_t>(co) * 9 + t) * cin;
-          for (int ci = 0; ci < cin; ++ci) one = fmaf(in ? xp[ci] : 0.f, wp[ci], one);
-        }
-        const float v = fmaf(one, a.scale[co], a.bias[co]);
-        mx = s == 0 ? v : fmaxf(mx, v);
-      }
-      dst[o + co] = fmaxf(mx, slope * mx);
-    }
-  } else {
+    // What the split could not carry: this wave's sums in plain float32, on the
+    // fp32 MFMA, operands straight from memory.  Tap by tap, 16 channels to four
+    // MFMAs, of which the r-th takes channels 4 q + r.
+    f32x4 sum[NT][MT];
 #pragma unroll
-    for (int i = 0; i < MT; ++i) {
-      int py, px;
-      const int o = row_out(i, &py, &px);
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int i = 0; i < MT; ++i) sum[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int t = 0; t < 9; ++t) {
+      const int ky = t / 3, kx = t - 3 * ky;
+      unsigned xo[MT], wo[NT];
+#pragma unroll
+      for (int i = 0; i < MT; ++i) {
+        const int r = wm * WM + i * 16 + (lane & 15);
+        int py, px;
+        block_pixel<BC>(r, &py, &px);
+        const int iy = by0 + py + ky - 1, ix = bx0 + px + kx - 1;
+        const bool ok = r < BR * BC && iy >= ry0 && iy < ry1 && ix >= rx0 && ix < rx1;
+        xo[i] = ok ? static_cast<unsigned>((((iy - tl.sy0) * tl.sw + (ix - tl.sx0)) * cin + 4 * q) * 4) : 0x80000000u;
+      }
 #pragma unroll
       for (int j = 0; j < NT; ++j) {
-        const int co = n0 + wn * WN + j * 16 + (POOL ? (lane & 15) : 4 * (lane >> 4));
-        float v[4];
-        if constexpr (POOL) {
+        const int co = n0 + wn * WN + j * 16 + (lane & 15);
+        wo[j] = co < cout ? static_cast<unsigned>(((co * 9 + t) * cin + 4 * q) * 4) : 0x80000000u;
+      }
+#pragma unroll 1
+      for (unsigned c = 0; c < static_cast<unsigned>(cin) * 4; c += 128) {  // 32 channels, their loads in flight together
+        u32x4 xv[2][MT], wv[2][NT];
 #pragma unroll
-          for (int k = 0; k < 4; ++k) v[k] = fmaf(acc[j][i][k], sc[j][0], bi[j][0]);
-          float mx = fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3]));
-          mx = fmaxf(mx, slope * mx);
-          if (o >= 0 && co < cout) dst[o + co] = mx;
-        } else {
+        for (int h = 0; h < 2; ++h) {
 #pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            v[k] = fmaf(acc[j][i][k], sc[j][k], bi[j][k]);
-            v[k] = fmaxf(v[k], slope * v[k]);
-          }
-          if (o >= 0 && co < cout) store4<MAFAT_F32>(dst + o + co, v);
+          for (int i = 0; i < MT; ++i) xv[h][i] = buf_load16(rsa, xo[i] + c + 64 * h);
+#pragma unroll
+          for (int j = 0; j < NT; ++j) wv[h][j] = buf_load16(rsb, wo[j] + c + 64 * h);
         }
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+              for (int j = 0; j < NT; ++j) {
+                const float x = __uint_as_float(xv[h][i][r]), w = __uint_as_float(wv[h][j][r]);
+                sum[j][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(POOL ? x : w, POOL ? w : x, sum[j][i], 0, 0, 0);
+              }
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int i = 0; i < MT; ++i) acc[j][i] = sum[j][i];
+  }
+#pragma unroll
+  for (int i = 0; i < MT; ++i) {
+    int py, px;
+    const int o = row_out(i, &py, &px);
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+      const int co = n0 + wn * WN + j * 16 + (POOL ? (lane & 15) : 4 * (lane >> 4));
+      float v[4];
+      if constexpr (POOL) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = fmaf(acc[j][i][k], sc[j][0], bi[j][0]);
+        float mx = fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3]));
+        mx = fmaxf(mx, slope * mx);
+        if (o >= 0 && co < cout) dst[o + co] = mx;
+      } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          v[k] = fmaf(acc[j][i][k], sc[j][k], bi[j][k]);
+          v[k] = fmaxf(v[k], slope * v[k]);
+        }
+        if (o >= 0 && co < cout) store4<MAFAT_F32>(dst + o + co, v);
       }
     }
   }

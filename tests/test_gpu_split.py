@@ -163,3 +163,33 @@ def test_split_special(kind, pool):
         for part in (np.s_[0, : 8 // (2 if pool else 1), : 16 // (2 if pool else 1)], np.s_[0]):
             m = np.max(np.abs(ref[part]))
             assert np.max(np.abs(out[part] - ref[part])) <= 4 * np.sqrt(9 * cin) * 2.0 ** -24 * m + 2.0 ** -148
+
+
+def test_split_special_time():
+    # A NaN in every window has every output computed again in plain float32: on the fp32 MFMA that takes some times as long
+    # as the layer, not the hundreds of times of one thread per output.
+    require_gpu()
+    import torch
+    from paper_2107_06960_amd import mafat as M
+    h, w, cin, cout = 26, 26, 512, 512
+    par = W.make_inputs([W.conv(cout)], h, w, cin, 1, 5, "f32")
+    net = M.Network(M.Plan([W.conv(cout)], (h, w, cin), "1x1"), par, 1, "f32")
+
+    def us(x):
+        t = []
+        for _ in range(9):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            net.run(x)
+            b.record()
+            b.synchronize()
+            t.append(a.elapsed_time(b) * 1e3)
+        return sorted(t)[len(t) // 2]
+
+    x = net.input_tensor(par["x"])
+    plain = us(x)
+    x[..., 7] = float("nan")
+    special = us(x)
+    print(f"[split] 3x3 512->512 on 26x26: {plain:.1f} us, with a NaN in every window {special:.1f} us", flush=True)
+    assert torch.isnan(net.y).all()
+    assert special <= 8 * plain
