@@ -23,10 +23,10 @@
 //
 // What the split cannot carry: infinities and NaN (their parts are not sums),
 // operands from 2^104 and sums of products from 2^80 up (2^48 times that is
-// past the largest float).  A wave whose accumulators hold anything not finite
-// is computed again in plain float32, on the fp32 MFMA with its operands straight
-// from memory, before it is stored: one such pixel in an early layer reaches all
-// waves of the later ones, so their time has to stay that of a convolution.
+// past the largest float).  Sums that come out not finite are computed again in
+// plain float32, on the fp32 MFMA with operands straight from memory, by their
+// whole wave: one such pixel in an early layer reaches all waves of the later
+// ones, so their time has to stay that of a convolution.
 // 3x3 512->512 on 26x26 with a NaN in every window takes 156 us (60 without), and
 // 4984 us with one output after the other on the vector ALUs.
 //
@@ -336,6 +336,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void conv_split_kernel(const StageA
     const int oy = POOL ? (by0 + *py) >> 1 : by0 + *py, ox = POOL ? (bx0 + *px) >> 1 : bx0 + *px;
     return ((oy - tl.dy0) * tl.dw + (ox - tl.dx0)) * cout;
   };
+  const auto carried = [](float v) { return fabsf(v) <= 3.4028234663852886e38f; };  // finite
   bool bad = false;
 #pragma unroll
   for (int j = 0; j < NT; ++j)
@@ -344,7 +345,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void conv_split_kernel(const StageA
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         acc[j][i][r] = (acc[j][i][r] + low[j][i][r]) * (1.f / kSplitScale / kSplitScale);
-        bad = bad || !(fabsf(acc[j][i][r]) <= 3.4028234663852886e38f);
+        bad = bad || !carried(acc[j][i][r]);
       }
   if (__builtin_expect(__builtin_amdgcn_ballot_w64(bad) != 0, 0)) {
     // What the split could not carry: this wave's sums in plain float32, on the
@@ -396,10 +397,14 @@ __global__ __launch_bounds__(64 * WGM * WGN) void conv_split_kernel(const StageA
               }
       }
     }
+    // Sum by sum: which others share a wave follows the block shape, and that
+    // the size of the launch; what an output gets must not.
 #pragma unroll
     for (int j = 0; j < NT; ++j)
 #pragma unroll
-      for (int i = 0; i < MT; ++i) acc[j][i] = sum[j][i];
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[j][i][r] = carried(acc[j][i][r]) ? acc[j][i][r] : sum[j][i][r];
   }
 #pragma unroll
   for (int i = 0; i < MT; ++i) {

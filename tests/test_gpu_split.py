@@ -193,3 +193,40 @@ def test_split_special_time():
     print(f"[split] 3x3 512->512 on 26x26: {plain:.1f} us, with a NaN in every window {special:.1f} us", flush=True)
     assert torch.isnan(net.y).all()
     assert special <= 8 * plain
+
+
+# Small launches take smaller blocks than those of all tiles or frames: other outputs share a wave.
+@pytest.mark.parametrize("pool", [False, True])
+@pytest.mark.parametrize("kind", ["inf", "nan", "huge"])
+def test_split_special_bits(kind, pool):
+    # which outputs the split could not carry, and what they get, does not follow the blocks: the same bits all tiles at once,
+    # one and two at a time, and for a frame alone
+    require_gpu()
+    import torch
+    from paper_2107_06960_amd import mafat as M
+    h, w, cin, cout, batch = 60, 52, 64, 128, 3
+    layers = [W.conv(cout)] + ([W.maxpool()] if pool else [])
+    par = W.make_inputs(layers, h, w, cin, batch, 5, "f32")
+    x = par["x"]
+    v = {"inf": np.inf, "nan": np.nan, "huge": 3e38}[kind]
+    for f in range(batch):
+        x[f, 13, 9 + f, 3] = v
+        x[f, 40 + f, 30, 60] = v
+
+    def run(x, tile_batch):
+        print(f"[split bits] {kind} pool={pool} batch {len(x)} tile batch {tile_batch}", flush=True)
+        net = M.Network(M.Plan(layers, (h, w, cin), "3x3", tile_batch=tile_batch), par, len(x), "f32")
+        return net.run(net.input_tensor(x)).clone()
+
+    def same(a, b):
+        num = ~torch.isnan(a)
+        return torch.equal(num, ~torch.isnan(b)) and torch.equal(a[num], b[num])
+
+    base = run(x, 0)
+    assert torch.isfinite(base).float().mean() > 0.9
+    for tb in (1, 2):
+        equal = same(run(x, tb), base)
+        assert equal, tb
+    for f in range(batch):
+        equal = same(run(np.ascontiguousarray(x[f:f + 1]), 0)[0], base[f])
+        assert equal, f
