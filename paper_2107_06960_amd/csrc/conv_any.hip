@@ -23,7 +23,10 @@
 // Work split: BM pixels x BN channels per workgroup, KG groups of four waves
 // (2 x 2 over the block); group g takes the 128-byte part g of every K
 // stage, so a long K with few pixels runs in nstage / KG steps, and the
-// groups' sums meet in LDS at the end.  These layers are small (a strided
+// groups' sums meet in LDS at the end.  Part p of K (128 bytes) belongs to
+// partial sum p mod 4 whatever KG is (a group keeps 4 / KG of them), and the four
+// are added in order: the block and the K groups, which follow the size of the
+// launch, change no bit of a result.  These layers are small (a strided
 // 3x3 on a 56x50 tile has 700 pixels): what bounds a launch is the chain of
 // K steps of one workgroup and how many compute units have one, not the
 // matrix cores, hence the small blocks and the K groups (choose_any in
@@ -81,8 +84,10 @@ __global__ __launch_bounds__(256 * KG) void conv_any_kernel(const StageArgs a) {
   constexpr int WM = BM / 2, WN = BN / 2, MT = WM / 16, NT = WN / 16;
   constexpr int RSB = BN * ESZ + 16;           // LDS bytes per staged output row
   constexpr int NPXO = POOL ? BM / 4 : BM;
+  constexpr int NP = 4 / KG;                   // partial sums of a group
+  static_assert(KG * NP == 4, "four partial sums");
   static_assert(APW >= 1 && BPW >= 1 && APW * 32 == BM && BPW * 32 == BN, "block shape");
-  static_assert(NPXO * RSB <= NS * SLOT && (KG - 1) * BM * BN * 4 <= NS * SLOT, "epilogue fits in the ring");
+  static_assert(NPXO * RSB <= NS * SLOT && (KG - 1) * NP * BM * BN * 4 <= NS * SLOT, "epilogue fits in the ring");
   __shared__ __align__(1024) unsigned char smem[NS * SLOT];
 
   KTile tl;
@@ -140,12 +145,14 @@ __global__ __launch_bounds__(256 * KG) void conv_any_kernel(const StageArgs a) {
     rd_a[h] = grp * PART + (wm * WM + (lane & 15)) * 128 + pos;
     rd_b[h] = grp * PART + (BM + wn * WN + (lane & 15)) * 128 + pos;
   }
-  f32x4 acc[NT][MT];
+  f32x4 part[NP][NT][MT];
 #pragma unroll
-  for (int j = 0; j < NT; ++j)
+  for (int u = 0; u < NP; ++u)
 #pragma unroll
-    for (int i = 0; i < MT; ++i) acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
-  auto compute = [&](int slot) {
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int i = 0; i < MT; ++i) part[u][j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto compute = [&](int slot, int u) {  // into partial sum u of this group's
     const unsigned char* sp = smem + slot * SLOT;
     u32x4 af[2][MT], bfr[2][NT];
 #pragma unroll
@@ -161,8 +168,8 @@ __global__ __launch_bounds__(256 * KG) void conv_any_kernel(const StageArgs a) {
       for (int i = 0; i < MT; ++i)
 #pragma unroll
         for (int j = 0; j < NT; ++j) {
-          if constexpr (POOL) mma<DT>(acc[j][i], af[h][i], bfr[h][j]);
-          else mma<DT>(acc[j][i], bfr[h][j], af[h][i]);
+          if constexpr (POOL) mma<DT>(part[u][j][i], af[h][i], bfr[h][j]);
+          else mma<DT>(part[u][j][i], bfr[h][j], af[h][i]);
         }
   };
 
@@ -194,12 +201,17 @@ __global__ __launch_bounds__(256 * KG) void conv_any_kernel(const StageArgs a) {
     for (int p = 0; p < NS - 1; ++p)
       if (p < nstage) issue(p);
     int slot = 0;
-    for (int s = 0; s < nstage; ++s) {
-      any_wait_stage<LPS, NS - 2>(nstage - 1 - s);
-      any_barrier();  // stage s is in LDS; every wave is done reading the slot before it
-      if (s + NS - 1 < nstage) issue(slot == 0 ? NS - 1 : slot - 1);
-      compute(slot);
-      slot = (slot == NS - 1) ? 0 : slot + 1;
+    for (int s0 = 0; s0 < nstage; s0 += NP) {
+#pragma unroll
+      for (int u = 0; u < NP; ++u) {
+        const int s = s0 + u;
+        if (s >= nstage) break;
+        any_wait_stage<LPS, NS - 2>(nstage - 1 - s);
+        any_barrier();  // stage s is in LDS; every wave is done reading the slot before it
+        if (s + NS - 1 < nstage) issue(slot == 0 ? NS - 1 : slot - 1);
+        compute(slot, u);
+        slot = (slot == NS - 1) ? 0 : slot + 1;
+      }
     }
   } else {
     // Values of this lane's pieces of the next stage, into registers.
@@ -251,35 +263,49 @@ __global__ __launch_bounds__(256 * KG) void conv_any_kernel(const StageArgs a) {
     };
     load();
     commit(0);
-    for (int s = 0; s < nstage; ++s) {
-      __syncthreads();  // stage s is in LDS; every wave is done reading the other slot
-      if (s + 1 < nstage) load();
-      compute(s & 1);
-      if (s + 1 < nstage) commit((s + 1) & 1);
+    for (int s0 = 0; s0 < nstage; s0 += NP) {
+#pragma unroll
+      for (int u = 0; u < NP; ++u) {
+        const int s = s0 + u;
+        if (s >= nstage) break;
+        __syncthreads();  // stage s is in LDS; every wave is done reading the other slot
+        if (s + 1 < nstage) load();
+        compute(s & 1, u);
+        if (s + 1 < nstage) commit((s + 1) & 1);
+      }
     }
   }
 
-  // The K groups' sums meet: group 0 adds the others' in order.
+  // The partial sums meet: group 0 adds the four in order.  Partial sum p is
+  // number p / KG of group p % KG.
   __syncthreads();  // every wave is done reading the ring
+  f32x4 acc[NT][MT];
+  f32x4* sx = reinterpret_cast<f32x4*>(smem);  // [(group - 1) * NP + number][wave of the group][NT][MT][64 lanes]
   if constexpr (KG > 1) {
-    f32x4* sx = reinterpret_cast<f32x4*>(smem);  // [group - 1][wave of the group][NT][MT][64 lanes]
     if (grp > 0) {
 #pragma unroll
-      for (int j = 0; j < NT; ++j)
-#pragma unroll
-        for (int i = 0; i < MT; ++i) sx[((((grp - 1) * 4 + wq) * NT + j) * MT + i) * 64 + lane] = acc[j][i];
-    }
-    __syncthreads();
-    if (grp == 0) {
-#pragma unroll
-      for (int g = 0; g < KG - 1; ++g)
+      for (int u = 0; u < NP; ++u)
 #pragma unroll
         for (int j = 0; j < NT; ++j)
 #pragma unroll
-          for (int i = 0; i < MT; ++i) acc[j][i] += sx[(((g * 4 + wq) * NT + j) * MT + i) * 64 + lane];
+          for (int i = 0; i < MT; ++i)
+            sx[(((((grp - 1) * NP + u) * 4 + wq) * NT + j) * MT + i) * 64 + lane] = part[u][j][i];
     }
     __syncthreads();
   }
+  if (grp == 0) {
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int i = 0; i < MT; ++i) {
+        acc[j][i] = part[0][j][i];
+#pragma unroll
+        for (int p = 1; p < 4; ++p)
+          acc[j][i] += p % KG == 0 ? part[p / KG][j][i]
+                                   : sx[((((p % KG - 1) * NP + p / KG) * 4 + wq) * NT + j) * MT * 64 + i * 64 + lane];
+      }
+  }
+  if constexpr (KG > 1) __syncthreads();
 
   // Epilogue (group 0): scale, bias, the fused pool, activation; the block's
   // outputs are staged in LDS as rows of BN channels.

@@ -1186,18 +1186,27 @@ extern "C" int mafat_plan_stage_kernel(const mafat_plan* plan, int32_t group, in
   return MAFAT_OK;
 }
 
-#ifdef MAFAT_TUNING
-// Tuning builds only: the configuration the runtime picks for stage s of
-// group g: kind, bm, bn, depth, kg, 0, br, bc.
-extern "C" int mafat_debug_config(const mafat_plan* plan, int32_t g, int32_t s, int32_t batch, int32_t dtype,
-                                  int32_t* out) {
-  const mafat::Stage& S = plan->groups[g].stages[s];
-  const mafat::StageConfig c = mafat::choose_config(S, batch, dtype, 1.0);
-  const int32_t v[8] = {c.kind, c.bm, c.bn, c.depth, c.kg, 0, c.br, c.bc};
-  for (int k = 0; k < 8; ++k) out[k] = v[k];
-  return 0;
+// Not part of the interface: the kernel and block the runtime picks for a stage
+// run by itself, for tests that have to reach a certain one: kind (KernelKind),
+// bm, bn, depth, kg, br, bc, and whether the convolution fetches ragged channels
+// value by value.
+extern "C" int mafat_debug_config(const mafat_plan* plan, int32_t group, int32_t stage, int32_t batch, int32_t dtype,
+                                  int32_t out[8]) {
+  clear_error();
+  if (!plan || !out || group < 0 || group >= static_cast<int>(plan->groups.size()) || stage < 0 ||
+      stage >= static_cast<int>(plan->groups[static_cast<size_t>(group)].stages.size()) || batch < 1 ||
+      (dtype != MAFAT_F32 && dtype != MAFAT_BF16)) {
+    set_error("plan and out must be non-NULL, group, stage, batch and dtype valid");
+    return MAFAT_EINVAL;
+  }
+  const Group& G = plan->groups[static_cast<size_t>(group)];
+  const Stage& S = G.stages[static_cast<size_t>(stage)];
+  const StageConfig c = stage_config(*plan, G, S, batch, dtype);
+  const int32_t v[8] = {c.kind, c.bm, c.bn, c.depth, c.kg, c.br, c.bc,
+                        c.kind == K_CONV_ANY && S.cin % (dtype == MAFAT_BF16 ? 8 : 4) != 0};
+  std::copy(v, v + 8, out);
+  return MAFAT_OK;
 }
-#endif
 
 extern "C" int mafat_packed_weights_size(const mafat_plan* plan, int32_t layer, int32_t dtype, size_t* bytes) {
   clear_error();

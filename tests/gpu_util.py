@@ -35,6 +35,19 @@ def run_gpu(layers, h, w, c, params, tiling, batch, dtype, x=None, want_cuts=Tru
     return (out, cuts, net, xt) if want_cuts else out
 
 
+KERNELS = ["mfma", "direct", "pool", "rgb", "rgb_mfma", "ring", "patch", "any", "split", "thin"]
+
+
+def stage_config(plan, batch, dtype, group=0, stage=0):
+    """What the runtime picks for a stage run by itself (host code, no GPU): the kernel's name, bm, bn, depth, kg, br, bc
+    and whether it fetches ragged channels value by value."""
+    import ctypes
+    from paper_2107_06960_amd import mafat as M
+    v = (ctypes.c_int32 * 8)()
+    assert M.lib().mafat_debug_config(ctypes.c_void_p(plan.handle), group, stage, batch, M.DTYPES[dtype], v) == 0
+    return dict(zip(("kernel", "bm", "bn", "depth", "kg", "br", "bc", "gather"), [KERNELS[v[0]], *v[1:]]))
+
+
 def normwise_err(got, ref):
     """max |got - ref| / max |ref| (NaN if anything is NaN)."""
     got = np.asarray(got, np.float64)

@@ -12,7 +12,7 @@ import pytest
 
 from paper_2107_06960_amd import workloads as W
 
-from gpu_util import TOL, normwise_err, require_gpu, run_gpu
+from gpu_util import TOL, normwise_err, require_gpu, run_gpu, stage_config
 
 pytestmark = pytest.mark.gpu
 
@@ -49,3 +49,33 @@ def test_any_filter(orc, case, dtype):
         out = run_gpu(layers, h, w, cin, par, tiling, batch, dtype, want_cuts=False, **kw)
         err = normwise_err(out, ref)
         assert err <= TOL[dtype], (kw, err)
+
+
+# (c_in, c_out, f, s, p, h, w, pool, batch): one frame of them takes more K groups than a batch
+BATCHED = [(32, 64, 3, 2, 1, 112, 100, False, 4), (32, 64, 3, 2, 1, 112, 100, False, 16), (128, 256, 3, 2, 1, 76, 76, False, 8),
+           (64, 64, 5, 1, 2, 28, 26, True, 24), (90, 16, 3, 1, 1, 40, 40, True, 16), (130, 96, 3, 1, 1, 40, 38, False, 16),
+           (132, 128, 3, 1, 1, 100, 96, True, 4)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", BATCHED, ids=lambda c: "-".join(str(v) for v in c))
+def test_any_filter_frame_in_a_batch(case, dtype):
+    # the block and the K groups follow the batch, a frame's bits do not
+    require_gpu()
+    import torch
+    from paper_2107_06960_amd import mafat as M
+    cin, cout, f, s, p, h, w, pool, batch = case
+    layers = [W.conv(cout, f, s=s, p=p)] + ([W.maxpool()] if pool else [])
+    par = W.make_inputs(layers, h, w, cin, batch, 13, dtype)
+    plan = M.Plan(layers, (h, w, cin), "2x1")
+    print(f"[any filter] {case} {dtype}: one frame {stage_config(plan, 1, dtype)}, all {stage_config(plan, batch, dtype)}",
+          flush=True)
+
+    def run(x):
+        net = M.Network(plan, par, len(x), dtype)
+        return net.run(net.input_tensor(x)).clone()
+
+    base = run(par["x"])
+    for k in (0, batch // 2, batch - 1):
+        equal = torch.equal(run(np.ascontiguousarray(par["x"][k:k + 1]))[0], base[k])
+        assert equal, k
