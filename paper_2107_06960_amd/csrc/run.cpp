@@ -127,6 +127,38 @@ bool choose_thin(const Stage& S, int batch, int dtype, double share, StageConfig
   return false;
 }
 
+// Layers of so few products that the vector ALUs take less time than the
+// matrix-core kernels' workgroups do to start (-1: those).  From 2176 layers and
+// launches (1 to 24 channels to 1 to 16, 1x1 to 5x5, strides 1 and 2, pooled or
+// not, 64x57 to 416x374, one and eight frames), us a launch, vector ALUs and
+// matrix cores: 3x3 3->8 on 416x374, eight frames, fp32 21.4 and 41.4, pooled 14.0
+// and 39.4; 3->16 37.4 and 42.1, pooled 23.8 and 39.3, but 6.9 and 4.8 on one
+// 64x57 frame; 1x1 1->1 on 400x360, eight frames, 10.3 and 26.1; 1x1 8->2 on one
+// 400x360 frame 7.4 and 17.4, on 64x57 5.3 and 4.3.  fp32 sums of few input
+// channels (conv_thin.hip) have the same bits on either; the others' choice must
+// not follow the launch or the batch, so it goes by one frame's outputs.
+int vector_kind(const Stage& S, int batch, int dtype, double share) {
+  const bool f32 = dtype == MAFAT_F32;
+  int64_t frame = 0;
+  for (const TileGeom& T : S.tiles) frame += static_cast<int64_t>(T.ch) * T.cw;
+  const double launch = static_cast<double>(frame) * batch * share;
+  if (rgb_ok(S)) {
+    if (f32) return S.cout <= 16 && (!S.pool || launch >= 32768) ? K_CONV_RGB : -1;
+    return S.cout == 8 && (S.pool ? frame >= 32768 : frame < 65536) ? K_CONV_RGB : -1;
+  }
+  if (S.cout > 8) return -1;  // one pass over the window
+  const int64_t K = static_cast<int64_t>(S.f) * S.f * S.cin;
+  int64_t limit;
+  if (S.cin % (f32 ? 4 : 8) != 0) {
+    const double size = f32 ? launch : static_cast<double>(frame);
+    limit = f32 && size >= (1 << 19) ? (S.pool ? 64 : 24) : size >= 16384 ? (S.pool ? 8 : 12) : (S.pool ? 4 : 8);
+  } else {
+    if (K > (S.pool ? 8 : 16)) return -1;
+    limit = frame >= 65536 ? (S.pool ? 16 : 36) : frame >= 16384 && !S.pool ? 16 : 0;
+  }
+  return K * S.cout <= limit ? K_CONV_DIRECT : -1;
+}
+
 // Block shape and K groups of the any-filter kernel, from a model of one
 // compute unit fitted to a sweep of eleven layers (7x7/2 to 1x1/2, both data
 // types, 18x16 to 224x200; within 15 % of most points): a workgroup costs
@@ -328,6 +360,8 @@ StageConfig choose_config(const Stage& S, int batch, int dtype, double share) {
       // bf16 first layer with 16/32/64 outputs: K = 27 padded to one MFMA K.
       c.kind = K_CONV_RGB_MFMA;
       c.bn = S.cout;
+    } else if (const int kind = vector_kind(S, batch, dtype, share); kind >= 0) {
+      c.kind = kind;
     } else if (choose_thin(S, batch, dtype, share, &c)) {
       c.kind = K_CONV_THIN;
     } else if (any_ok(S, dtype)) {
