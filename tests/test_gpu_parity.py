@@ -295,6 +295,54 @@ def test_two_gib_input_frame(orc, dtype, hwc):
         assert err <= TOL[dtype], ((y0, y1, x0, x1), err)
 
 
+# (c_in, c_out, f, s, p, pool, h, w, dtype, kernel): frames of 2^31 bytes and a little more, and what takes them
+HUGE = [(3, 32, 3, 1, 1, True, 13400, 13372, "f32", "rgb"),      # at smaller sizes the thin-input kernel
+        (3, 8, 3, 1, 1, False, 13390, 13381, "f32", "rgb"),
+        (64, 8, 3, 1, 1, True, 4100, 4094, "bf16", "direct"),
+        (64, 16, 1, 1, 0, True, 2900, 2894, "f32", "direct"),
+        (64, 24, 3, 2, 0, False, 4098, 4099, "bf16", "direct"),
+        (32, 8, 5, 1, 2, True, 4098, 4101, "f32", "direct"),
+        (7, 9, 4, 3, 2, False, 8759, 8761, "f32", "direct")]
+
+
+@pytest.mark.parametrize("case", HUGE, ids=lambda c: "-".join(str(v) for v in c))
+def test_huge_input_frame(orc, case):
+    # Past 32-bit byte offsets: the vector-ALU kernels, every form of them; all outputs written, sampled rectangles (corners,
+    # edges, tile seams, interior) against the oracle on the rows and columns they read.
+    import torch
+    from paper_2107_06960_amd import mafat as M
+    from gpu_util import stage_config
+    cin, cout, f, s, p, pool, h, w, dtype, kernel = case
+    print(f"[parity] huge frame {case}", flush=True)
+    layers = [W.conv(cout, f, s=s, p=p)] + ([W.maxpool()] if pool else [])
+    plan = M.Plan(layers, (h, w, cin), "2x2")
+    assert h * w * cin * (2 if dtype == "bf16" else 4) >= 2 ** 31
+    assert stage_config(plan, 1, dtype)["kernel"] == kernel
+    par = W.make_inputs(layers, 16, 16, cin, 1, 73, dtype)
+    net = M.Network(plan, par, 1, dtype)
+    gen = torch.Generator(device="cuda").manual_seed(73)
+    x = torch.empty((1, h, w, cin), dtype=net.tdtype, device="cuda")
+    for r in range(0, h, 1024):  # steps of 1/256: exact in bf16
+        part = x[:, r:r + 1024]
+        part.copy_(torch.randint(-128, 128, part.shape, generator=gen, device="cuda", dtype=torch.int16) / 256)
+    net.y.fill_(float("nan"))
+    y = net.run(x)
+    assert not torch.isnan(y).any()
+    k = 2 if pool else 1
+    ho, wo = y.shape[1:3]
+    m = 2 * (f + 1)  # conv outputs beside the rectangle: past the oracle's own padding
+    for (y0, y1, x0, x1) in [(0, 2, 0, 2), (ho - 2, ho, wo - 2, wo), (0, 2, wo // 2 - 1, wo // 2 + 1),
+                             (ho // 2 - 1, ho // 2 + 1, 0, 2), (ho // 2 - 1, ho // 2 + 1, wo // 2 - 1, wo // 2 + 1),
+                             (1234, 1238, 777, 781), (ho - 5, ho, 3, 9)]:
+        a0, b0 = (max(0, k * (v - m)) for v in (y0, x0))  # first conv outputs computed
+        a1, b1 = min(h, (k * y1 + m) * s + f), min(w, (k * x1 + m) * s + f)
+        crop = x[:, a0 * s:a1, b0 * s:b1].float().cpu().numpy()
+        ref = orc.forward_layers(layers, crop.shape[1], crop.shape[2], cin, crop, par)[0]
+        ref = ref[y0 - a0 // k:y1 - a0 // k, x0 - b0 // k:x1 - b0 // k]
+        err = normwise_err(y[0, y0:y1, x0:x1].float().cpu().numpy(), ref)
+        assert err <= TOL[dtype], ((y0, y1, x0, x1), err)
+
+
 def test_pack_weights_kernel_layout():
     # the repack kernel against the layout written out with torch ops:
     # [cout/BN][cin/32][9][BN][32], rows past c_out zero
