@@ -163,4 +163,18 @@ int run_network_impl(const mafat_plan* plan, int batch, int dtype, const void* x
 // Thread-local error detail (mafat_last_error).
 void set_error(const std::string& msg);
 void clear_error();
+int host_failure() noexcept;  // the error of a host allocation that failed: its message and status
+
+// What a C entry runs: no exception leaves it.
+template <typename F>
+int guarded(F&& entry) noexcept {
+  try {
+    return entry();
+  } catch (...) {  // std::bad_alloc; std::system_error of a mutex
+    return host_failure();
+  }
+}
+
+// Bytes of workspace of a plan (arguments checked by the caller; may throw).
+size_t workspace_bytes(const mafat_plan& P, int batch, int dtype);
 }  // namespace mafat

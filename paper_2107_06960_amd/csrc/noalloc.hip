@@ -44,39 +44,41 @@ using namespace mafat;
 extern "C" int mafat_run_network_static(const mafat_plan* plan, int32_t batch, int32_t dtype, const void* x,
                                         void* y, void* const* cut_bufs, const void* const* w,
                                         const float* const* scale, const float* const* bias, void* stream) {
-  clear_error();
-  if (!plan) return fail(MAFAT_EINVAL, "plan is NULL");
-  size_t need = 0;
-  const int rc = mafat_workspace_size(plan, batch, dtype, &need);
-  if (rc != MAFAT_OK) return fail(rc, "batch must be >= 1 and dtype F32 or BF16");
-  if (need > kStaticWorkspaceBytes)
-    return fail(MAFAT_EWORKSPACE, "the plan needs " + std::to_string(need) + " bytes of workspace for batch " +
-                                      std::to_string(batch) + "; the static workspace holds " +
-                                      std::to_string(kStaticWorkspaceBytes) +
-                                      " (use mafat_run_network with a caller buffer)");
-  int dev = -1;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices)
-    return fail(MAFAT_EHIP, "no current HIP device (or device index >= 64)");
-  if (stream) {
-    int sdev = -1;
-    if (hipStreamGetDevice(static_cast<hipStream_t>(stream), &sdev) != hipSuccess)
-      return fail(MAFAT_EHIP, "hipStreamGetDevice failed");
-    if (sdev != dev)
-      return fail(MAFAT_EINVAL, "the stream belongs to device " + std::to_string(sdev) + " but device " +
-                                    std::to_string(dev) + " is current");
-  }
-  void* ws = nullptr;
-  {
-    std::lock_guard<std::mutex> lock(g_mu);
-    if (!g_scratch_ptr[dev]) {
-      void* p = nullptr;
-      const hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
-      if (e != hipSuccess || !p)
-        return fail(MAFAT_EHIP, std::string("hipGetSymbolAddress of the static workspace failed: ") +
-                                    hipGetErrorString(e));
-      g_scratch_ptr[dev] = p;
+  return guarded([&] {
+    clear_error();
+    if (!plan) return fail(MAFAT_EINVAL, "plan is NULL");
+    size_t need = 0;
+    const int rc = mafat_workspace_size(plan, batch, dtype, &need);
+    if (rc != MAFAT_OK) return fail(rc, "batch must be >= 1 and dtype F32 or BF16");
+    if (need > kStaticWorkspaceBytes)
+      return fail(MAFAT_EWORKSPACE, "the plan needs " + std::to_string(need) + " bytes of workspace for batch " +
+                                        std::to_string(batch) + "; the static workspace holds " +
+                                        std::to_string(kStaticWorkspaceBytes) +
+                                        " (use mafat_run_network with a caller buffer)");
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices)
+      return fail(MAFAT_EHIP, "no current HIP device (or device index >= 64)");
+    if (stream) {
+      int sdev = -1;
+      if (hipStreamGetDevice(static_cast<hipStream_t>(stream), &sdev) != hipSuccess)
+        return fail(MAFAT_EHIP, "hipStreamGetDevice failed");
+      if (sdev != dev)
+        return fail(MAFAT_EINVAL, "the stream belongs to device " + std::to_string(sdev) + " but device " +
+                                      std::to_string(dev) + " is current");
     }
-    ws = g_scratch_ptr[dev];
-  }
-  return run_network_impl(plan, batch, dtype, x, y, cut_bufs, w, scale, bias, ws, kStaticWorkspaceBytes, stream);
+    void* ws = nullptr;
+    {
+      std::lock_guard<std::mutex> lock(g_mu);
+      if (!g_scratch_ptr[dev]) {
+        void* p = nullptr;
+        const hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
+        if (e != hipSuccess || !p)
+          return fail(MAFAT_EHIP, std::string("hipGetSymbolAddress of the static workspace failed: ") +
+                                      hipGetErrorString(e));
+        g_scratch_ptr[dev] = p;
+      }
+      ws = g_scratch_ptr[dev];
+    }
+    return run_network_impl(plan, batch, dtype, x, y, cut_bufs, w, scale, bias, ws, kStaticWorkspaceBytes, stream);
+  });
 }

@@ -16,6 +16,19 @@ namespace mafat {
 static thread_local std::string g_last_error;
 void set_error(const std::string& msg) { g_last_error = msg; }
 void clear_error() { g_last_error.clear(); }
+int host_failure() noexcept {
+  try {
+    set_error("host allocation failed");
+  } catch (...) {
+    clear_error();
+  }
+  return MAFAT_ENOMEM;
+}
+size_t workspace_bytes(const mafat_plan& P, int batch, int dtype) {
+  size_t best = 0;
+  for (const Group& G : P.groups) best = std::max(best, workspace_layout(P, G, batch, dtype).total);
+  return best;
+}
 
 namespace {
 
@@ -708,10 +721,10 @@ extern "C" int mafat_workspace_size(const mafat_plan* plan, int32_t batch, int32
                                     size_t* bytes) {
   if (!plan || !bytes || batch < 1) return MAFAT_EINVAL;
   if (dtype != MAFAT_F32 && dtype != MAFAT_BF16) return MAFAT_EUNSUPPORTED;
-  size_t best = 0;
-  for (const Group& G : plan->groups) best = std::max(best, workspace_layout(*plan, G, batch, dtype).total);
-  *bytes = best;
-  return MAFAT_OK;
+  return guarded([&] {
+    *bytes = workspace_bytes(*plan, batch, dtype);
+    return MAFAT_OK;
+  });
 }
 
 extern "C" const char* mafat_status_string(int status) {

@@ -86,7 +86,7 @@ int64_t device_bytes(const mafat_plan& P, int batch, int dtype, bool one_tile) {
   }
   size_t ws = 0;
   if (!one_tile) {
-    mafat_workspace_size(&P, batch, dtype, &ws);
+    ws = workspace_bytes(P, batch, dtype);
   } else {  // the workspace of tile batch 1: one tile slot per scratch buffer
     for (const Group& G : P.groups) {
       if (G.reuse) {  // its tile rows run one after another already
@@ -128,7 +128,7 @@ extern "C" int mafat_predict_mem(const mafat_plan* plan, int32_t model, int32_t 
     set_error("unknown memory model");
     return MAFAT_EINVAL;
   }
-  return predict(plan, model, batch, dtype, bytes);
+  return guarded([&] { return predict(plan, model, batch, dtype, bytes); });
 }
 
 namespace {
@@ -207,8 +207,10 @@ extern "C" int mafat_get_config(const mafat_layer* layers, int32_t n_layers, int
                                 int64_t limit_bytes, const int32_t* cuts, int32_t n_cuts, const int32_t* grids,
                                 int32_t n_grids, int32_t second_grid, int32_t* out_cut, int32_t* out_grid1,
                                 int32_t* out_grid2, int64_t* out_pred, int32_t* out_fits) {
-  return get_config(layers, n_layers, in_h, in_w, in_c, model, batch, dtype, bias_bytes, limit_bytes, cuts, n_cuts,
-                    grids, n_grids, second_grid, 0, false, out_cut, out_grid1, out_grid2, out_pred, out_fits);
+  return guarded([&] {
+    return get_config(layers, n_layers, in_h, in_w, in_c, model, batch, dtype, bias_bytes, limit_bytes, cuts, n_cuts,
+                      grids, n_grids, second_grid, 0, false, out_cut, out_grid1, out_grid2, out_pred, out_fits);
+  });
 }
 
 extern "C" int mafat_get_config_balanced(const mafat_layer* layers, int32_t n_layers, int32_t in_h,

@@ -756,8 +756,7 @@ int run_group_impl(const mafat_plan* plan, int g, int s_begin, int s_end, int ba
                    void* ws, size_t ws_bytes, hipStream_t stream, void* const* events) {
   const Group& G = plan->groups[g];
   const size_t esz = (dtype == MAFAT_F32) ? 4 : 2;
-  size_t need = 0;
-  mafat_workspace_size(plan, batch, dtype, &need);
+  const size_t need = workspace_bytes(*plan, batch, dtype);
   if (ws_bytes < need)
     return fail(MAFAT_EWORKSPACE, "workspace " + std::to_string(ws_bytes) + " < " + std::to_string(need) + " bytes");
   if (need > 0 && (!ws || (reinterpret_cast<uintptr_t>(ws) & 255u)))
@@ -1101,8 +1100,10 @@ extern "C" int mafat_run_group(const mafat_plan* plan, int32_t group, int32_t ba
                                const void* x, void* y, const void* const* w,
                                const float* const* scale, const float* const* bias,
                                void* workspace, size_t ws_bytes, void* stream) {
-  clear_error();
-  return run_group_checked(plan, group, batch, dtype, x, y, w, scale, bias, workspace, ws_bytes, stream, nullptr);
+  return guarded([&] {
+    clear_error();
+    return run_group_checked(plan, group, batch, dtype, x, y, w, scale, bias, workspace, ws_bytes, stream, nullptr);
+  });
 }
 
 extern "C" int mafat_run_group_timed(const mafat_plan* plan, int32_t group, int32_t batch, int32_t dtype,
@@ -1110,26 +1111,30 @@ extern "C" int mafat_run_group_timed(const mafat_plan* plan, int32_t group, int3
                                      const float* const* scale, const float* const* bias,
                                      void* workspace, size_t ws_bytes, void* stream,
                                      void* const* events) {
-  clear_error();
-  if (!events) return fail(MAFAT_EINVAL, "events is NULL (use mafat_run_group to run without timestamps)");
-  return run_group_checked(plan, group, batch, dtype, x, y, w, scale, bias, workspace, ws_bytes, stream, events);
+  return guarded([&] {
+    clear_error();
+    if (!events) return fail(MAFAT_EINVAL, "events is NULL (use mafat_run_group to run without timestamps)");
+    return run_group_checked(plan, group, batch, dtype, x, y, w, scale, bias, workspace, ws_bytes, stream, events);
+  });
 }
 
 extern "C" int mafat_run_stage(const mafat_plan* plan, int32_t group, int32_t stage, int32_t batch,
                                int32_t dtype, const void* x, void* y, const void* const* w,
                                const float* const* scale, const float* const* bias, void* workspace,
                                size_t ws_bytes, void* stream) {
-  clear_error();
-  int rc = check_common(plan, batch, dtype);
-  if (rc != MAFAT_OK) return rc;
-  if (group < 0 || group >= static_cast<int>(plan->groups.size()))
-    return fail(MAFAT_EINVAL, "group index out of range");
-  if (stage < 0 || stage >= static_cast<int>(plan->groups[group].stages.size()))
-    return fail(MAFAT_EINVAL, "stage index out of range");
-  if (plan->groups[group].tile_batch < plan->groups[group].ntiles || plan->groups[group].reuse)
-    return fail(MAFAT_EUNSUPPORTED, "the group runs in tile batches or rows: its stages cannot run one at a time");
-  return run_group_impl(plan, group, stage, stage + 1, batch, dtype, x, y, w, scale, bias, workspace, ws_bytes,
-                        static_cast<hipStream_t>(stream), nullptr);
+  return guarded([&] {
+    clear_error();
+    int rc = check_common(plan, batch, dtype);
+    if (rc != MAFAT_OK) return rc;
+    if (group < 0 || group >= static_cast<int>(plan->groups.size()))
+      return fail(MAFAT_EINVAL, "group index out of range");
+    if (stage < 0 || stage >= static_cast<int>(plan->groups[group].stages.size()))
+      return fail(MAFAT_EINVAL, "stage index out of range");
+    if (plan->groups[group].tile_batch < plan->groups[group].ntiles || plan->groups[group].reuse)
+      return fail(MAFAT_EUNSUPPORTED, "the group runs in tile batches or rows: its stages cannot run one at a time");
+    return run_group_impl(plan, group, stage, stage + 1, batch, dtype, x, y, w, scale, bias, workspace, ws_bytes,
+                          static_cast<hipStream_t>(stream), nullptr);
+  });
 }
 
 int mafat::run_network_impl(const mafat_plan* plan, int batch, int dtype, const void* x, void* y,
@@ -1155,8 +1160,10 @@ extern "C" int mafat_run_network(const mafat_plan* plan, int32_t batch, int32_t 
                                  const void* const* w, const float* const* scale,
                                  const float* const* bias, void* workspace, size_t ws_bytes,
                                  void* stream) {
-  clear_error();
-  return run_network_impl(plan, batch, dtype, x, y, cut_bufs, w, scale, bias, workspace, ws_bytes, stream);
+  return guarded([&] {
+    clear_error();
+    return run_network_impl(plan, batch, dtype, x, y, cut_bufs, w, scale, bias, workspace, ws_bytes, stream);
+  });
 }
 
 extern "C" int mafat_plan_stage_fused(const mafat_plan* plan, int32_t group, int32_t stage, int32_t batch,
