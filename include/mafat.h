@@ -31,9 +31,13 @@
  *     floor((in + 2p - f) / s) + 1.  A max-pool takes the maximum over the
  *     in-image elements of its window.  3x3 and 1x1 "same" convolutions
  *     (s = 1, p = (f-1)/2) run on the matrix cores, a 2x2/2 max-pool after
- *     a convolution in its epilogue; other convolutions on a matrix-core
- *     kernel for any filter (vector ALUs for frames of 2^31 bytes or more).
- *     Tensor extents must be at most 32767.
+ *     a convolution in its epilogue; other convolutions on matrix-core
+ *     kernels for any filter (vector ALUs for layers of few products and for
+ *     frames of 2^31 bytes or more).  Tensor extents must be at most 32767.
+ *   - Equal calls give equal bits.  A frame's results do not depend on the
+ *     frames beside it in a batch, but the batch size may change the order
+ *     of the sums, and so the last bits, of float32 1x1 convolutions and of
+ *     float32 3x3 ones whose input channels are no multiple of 32.
  *
  * Ownership and threading
  *   - A plan is created and destroyed by the library, read-only after
@@ -325,7 +329,7 @@ typedef enum {
   MAFAT_KERNEL_RING = 3,         /* bf16 implicit GEMM through an LDS ring (1x1 convolutions) */
   MAFAT_KERNEL_MFMA_F32 = 4,     /* float32 3x3 / 1x1 on the matrix cores */
   MAFAT_KERNEL_FIRST_LAYER = 5,  /* a 3-channel 3x3 first layer run alone */
-  MAFAT_KERNEL_GENERIC = 6,      /* any supported layer and size: matrix cores, or vector ALUs for frames past 2^31 bytes */
+  MAFAT_KERNEL_GENERIC = 6,      /* any supported layer and size: matrix cores, or vector ALUs (few products, frames past 2^31 bytes) */
   MAFAT_KERNEL_POOL = 7          /* a max-pool that does not follow a convolution */
 } mafat_kernel;
 

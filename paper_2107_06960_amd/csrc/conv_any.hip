@@ -11,11 +11,12 @@
 //     in one filter tap; it is fetched with buffer_load_dwordx4 ... lds
 //     straight into the LDS ring, each lane keeping the tap and channel of its
 //     piece and stepping them from stage to stage;
-//   - ragged channels (GATHER = true, e.g. c_in = 3): the f * c_in values of
-//     one filter row are one contiguous run of the NHWC input, and of the
-//     KRSC weights, so K runs over the f rows, each padded to whole pieces.
-//     A lane fetches the values of its piece one by one (their place need not
-//     be aligned), packs them and writes the piece to LDS.
+//   - ragged channels (GATHER = true: more of them than fit the LDS of
+//     conv_thin.hip): the f * c_in values of one filter row are one contiguous
+//     run of the NHWC input, and of the KRSC weights, so K runs over the f rows,
+//     each padded to whole pieces.  A lane fetches the values of its piece one
+//     by one (their place need not be aligned), packs them and writes the piece
+//     to LDS.
 // A value outside the image, past the end of K, past the tile's last pixel or
 // past c_out is fetched at an offset with bit 31 set, past the buffer
 // descriptor's range, and reads zero.
@@ -32,8 +33,8 @@
 // matrix cores, hence the small blocks and the K groups (choose_any in
 // run.cpp).  Measured against one thread per output pixel on the vector ALUs,
 // which these layers ran on before (strided stem on 224x200, four frames,
-// bf16): 7x7/2 3->32 374 -> 15 us, 3x3/2 32->64 1389 -> under 9 us, 5x5
-// 64->64 8774 -> under 9 us.
+// bf16): 3x3/2 32->64 1389 -> under 9 us, 5x5 64->64 8774 -> under 9 us.  The
+// four partial sums cost 0.7 % (528 layers and batches, 6 % at most).
 //
 // Requires byte offsets below 2^31 within a frame's source buffer and within
 // the weights (checked by the host); a fused pool needs even tile origins

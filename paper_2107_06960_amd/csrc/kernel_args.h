@@ -79,7 +79,7 @@ struct StageArgs {
 // Kernel families the runtime picks from.
 enum KernelKind {
   K_CONV_MFMA = 0,      // matrix cores, operands staged through registers (fp32)
-  K_CONV_DIRECT = 1,    // vector ALUs, any shape (frames past 32-bit byte offsets)
+  K_CONV_DIRECT = 1,    // vector ALUs, any shape (few products, frames past 32-bit byte offsets)
   K_POOL = 2,           // lone max-pool
   K_CONV_RGB = 3,       // 3-channel first layer, vector ALUs
   K_CONV_RGB_MFMA = 4,  // 3-channel first layer, matrix cores (bf16)

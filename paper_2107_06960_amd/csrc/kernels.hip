@@ -13,12 +13,14 @@
 //                       bf16: v_mfma_f32_16x16x32_bf16; fp32:
 //                       v_mfma_f32_16x16x4_f32.  Operand tiles are staged
 //                       global -> registers -> LDS (double buffered).
-//   conv_direct_kernel  vector-ALU direct convolution for frames too large for
+//   conv_direct_kernel  vector-ALU direct convolution for layers of few products
+//                       (vector_kind in run.cpp) and for frames too large for
 //                       32-bit byte offsets (the other kernels' buffer
 //                       descriptors): one thread per output pixel (or per 2x2
 //                       pool window), weights through the scalar cache.
 //   conv_rgb_kernel     the 3-channel first layer on the vector ALUs, patch in
-//                       registers, for frames past 32-bit byte offsets.
+//                       registers, for 8 and 16 outputs (vector_kind) and for
+//                       frames past 32-bit byte offsets.
 //   conv_rgb_mfma_kernel  the 3-channel first layer in bf16 on the matrix
 //                       cores, K = 27 zero-padded to 32.
 //   pool_kernel         a max-pool stage that does not follow a convolution.
@@ -826,8 +828,8 @@ __global__ __launch_bounds__(256) void conv_rgb_mfma_kernel(const StageArgs a) {
 //
 // Bound by memory: the input once, the output once.  3x3/2 on 112x112x64 bf16,
 // eight frames (16 MB): 27.0 us a call with four threads striding over a
-// pixel's channels two bytes at a time, 8.3 us now (of which the host takes
-// about 8).
+// pixel's channels two bytes at a time, 6.2 us now (of which the host takes
+// most).
 template <int DT, int F, bool VEC>
 __global__ __launch_bounds__(256) void pool_kernel(const StageArgs a) {
   if (__builtin_expect(blockIdx.y != 0, 0)) {  // the second grid row: carried band copies (row reuse)

@@ -39,7 +39,8 @@ int fail(int status, const std::string& msg) {
 // launch).
 // These and the first-layer kernels take "same" convolutions only: f = 1 or
 // 3, stride 1, padding (f - 1) / 2.  Every other convolution (and channel
-// count) runs on the any-filter kernel.
+// count) runs on the thin-input or the any-filter kernel, or, of few products,
+// on the vector ALUs.
 bool same_conv(const Stage& S) {
   return S.kind == STAGE_CONV && (S.f == 1 || S.f == 3) && S.s == 1 && S.p == (S.f - 1) / 2;
 }
@@ -51,7 +52,7 @@ bool mfma_ok(const Stage& S, int dtype) {
          static_cast<int64_t>(S.cout) * S.f * S.f * S.cin * esz < (1ll << 31);
 }
 
-// The vector first-layer kernel: 3 input channels, 3x3, 8/16/32/64 outputs.
+// A first layer of an image network: 3 input channels, 3x3, 8/16/32/64 outputs.
 bool rgb_ok(const Stage& S) {
   return same_conv(S) && S.cin == 3 && S.f == 3 &&
          (S.cout == 8 || S.cout == 16 || S.cout == 32 || S.cout == 64);
@@ -170,7 +171,8 @@ int vector_kind(const Stage& S, int batch, int dtype, double share) {
 // long K takes small blocks and several K groups (5x5 64->64 fp32 on nine
 // 19x17 tiles: 14.4 us with 32x32 blocks and four groups, 42.9 us with 64x64
 // and one), a larger one wider blocks (3x3/2 128->256 bf16 on 76x76, four
-// frames: 11.2 us with 128x64 and two groups, 15.8 us with 32x32 and one).
+// frames: 12.8 us with 64x32 and one group, 15.8 us with 32x32 and one).  The
+// choice changes no bit (conv_any.hip).
 void choose_any(const Stage& S, int batch, int dtype, StageConfig* c) {
   const int esz = (dtype == MAFAT_BF16) ? 2 : 4, epv = 16 / esz;
   const bool gather = S.cin % epv != 0;
