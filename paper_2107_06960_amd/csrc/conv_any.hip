@@ -47,27 +47,6 @@
 namespace mafat {
 namespace {
 
-typedef __attribute__((address_space(3))) void* lds_ptr_t;
-
-// Wait until at most N of this thread's vector memory loads are outstanding.
-template <int N>
-__device__ __forceinline__ void any_wait_vmcnt() {
-  static_assert(N >= 0 && N <= 63, "vmcnt range");
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-// Wait for the oldest stage when `rem` later ones (L loads each, at most R)
-// are in flight.
-template <int L, int R>
-__device__ __forceinline__ void any_wait_stage(int rem) {
-  if constexpr (R == 0) {
-    any_wait_vmcnt<0>();
-  } else {
-    if (rem >= R) any_wait_vmcnt<R * L>();
-    else any_wait_stage<L, R - 1>(rem);
-  }
-}
-__device__ __forceinline__ void any_barrier() { asm volatile("s_barrier" ::: "memory"); }
-
 template <int DT, int BM, int BN, int KG, bool POOL, bool GATHER>
 __global__ __launch_bounds__(256 * KG) void conv_any_kernel(const StageArgs a) {
   if (__builtin_expect(blockIdx.y != 0, 0)) {  // the second grid row: carried band copies (row reuse)
@@ -207,8 +186,8 @@ __global__ __launch_bounds__(256 * KG) void conv_any_kernel(const StageArgs a) {
       for (int u = 0; u < NP; ++u) {
         const int s = s0 + u;
         if (s >= nstage) break;
-        any_wait_stage<LPS, NS - 2>(nstage - 1 - s);
-        any_barrier();  // stage s is in LDS; every wave is done reading the slot before it
+        wait_stage<LPS, NS - 2>(nstage - 1 - s);
+        wg_barrier();  // stage s is in LDS; every wave is done reading the slot before it
         if (s + NS - 1 < nstage) issue(slot == 0 ? NS - 1 : slot - 1);
         compute(slot, u);
         slot = (slot == NS - 1) ? 0 : slot + 1;

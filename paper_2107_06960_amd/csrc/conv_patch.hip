@@ -90,31 +90,6 @@ MAFAT_WG_TRACE_DECL(g_wg_patch)
 #endif
 namespace {
 
-typedef __attribute__((address_space(3))) void* lds_ptr_t;
-
-template <int N>
-__device__ __forceinline__ void pwait_vmcnt() {
-  static_assert(N >= 0 && N <= 63, "vmcnt range");
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-template <int L, int R>
-__device__ __forceinline__ void pwait_stage(int rem) {
-  if constexpr (R == 0) {
-    pwait_vmcnt<0>();
-  } else {
-    if (rem >= R) {
-      pwait_vmcnt<R * L>();
-    } else {
-      pwait_stage<L, R - 1>(rem);
-    }
-  }
-}
-// The barrier alone: for slots that LDS DMA fills (pwait_vmcnt first) and that
-// are only read, their reads having been waited for by the MFMAs that use them.
-__device__ __forceinline__ void pbarrier() { asm volatile("s_barrier" ::: "memory"); }
-// After LDS writes of this wave that other waves read: they have to land first.
-__device__ __forceinline__ void pbarrier_writes() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 // N2 > 0: a 1x1 convolution with N2 outputs of this stage's output (all BN
 // = c_out channels in the block) follows in the same workgroup: the block's
 // activated bf16 outputs stay in LDS and are the A operand of a second GEMM
@@ -600,7 +575,7 @@ void conv_patch_kernel(const StageArgs a) {
     MAFAT_PTRACE(7);
     // The pooled values every wave has written are in the patch, and every wave
     // is done with the input patch: taps 5-8 load over it.
-    pbarrier_writes();
+    wg_barrier_writes();
 #pragma unroll
     for (int k = 0; k < NBW; ++k) {
       const int g = k * NWAVE + wave;
@@ -611,8 +586,8 @@ void conv_patch_kernel(const StageArgs a) {
     MAFAT_PTRACE(8);
     using I5 = std::integral_constant<int, 5>;
     taps(smem, smem, I0{}, I5{});  // taps 0-4 (their rows were in before the first layer started)
-    pwait_vmcnt<0>();
-    pbarrier();
+    wait_vmcnt<0>();
+    wg_barrier();
     MAFAT_PTRACE(9);
     taps(smem, smem, I5{}, I9{});
   } else if constexpr (N2 > 0) {
@@ -639,26 +614,26 @@ void conv_patch_kernel(const StageArgs a) {
         }
         issue_b_taps(Y, I0{}, IY{});
       }
-      pwait_vmcnt<NAW + YT>();           // chunk 0 is in
-      pbarrier();
+      wait_vmcnt<NAW + YT>();           // chunk 0 is in
+      wg_barrier();
       MAFAT_PTRACE(8);
       taps(smem, smem, I0{}, I9{});
-      pbarrier();                        // every wave is done with the slot
+      wg_barrier();                        // every wave is done with the slot
       issue_b_taps(smem, IY{}, I9{});    // chunk 1, taps [YT, 9), to the slot
-      pwait_vmcnt<9 - YT>();             // chunk 1's patch and first taps are in
-      pbarrier();
+      wait_vmcnt<9 - YT>();             // chunk 1's patch and first taps are in
+      wg_barrier();
       MAFAT_PTRACE(9);
       taps(Y, Y, I0{}, IY{});
-      pwait_vmcnt<0>();
-      pbarrier();
+      wait_vmcnt<0>();
+      wg_barrier();
       MAFAT_PTRACE(10);
       taps(Y, smem, IY{}, I9{});
     } else {
       for (int s = 0; s < nstage; ++s) {
-        if (s > 0) pbarrier();
+        if (s > 0) wg_barrier();
         issue(s, 0);
-        pwait_vmcnt<0>();
-        pbarrier();
+        wait_vmcnt<0>();
+        wg_barrier();
         compute(0);
       }
     }
@@ -666,10 +641,10 @@ void conv_patch_kernel(const StageArgs a) {
     // One slot (half the LDS, so two workgroups fit on a CU and hide each
     // other's load latency): load a chunk, wait, compute, repeat.
     for (int s = 0; s < nstage; ++s) {
-      if (s > 0) pbarrier();  // every wave is done reading the slot
+      if (s > 0) wg_barrier();  // every wave is done reading the slot
       issue(s, 0);
-      pwait_vmcnt<0>();
-      pbarrier();
+      wait_vmcnt<0>();
+      wg_barrier();
       MAFAT_PTRACE(8 + s);
       compute(0);
     }
@@ -679,8 +654,8 @@ void conv_patch_kernel(const StageArgs a) {
       if (p < nstage) issue(p, p);
     int slot = 0;
     for (int s = 0; s < nstage; ++s) {
-      pwait_stage<LPS, NS - 2>(nstage - 1 - s);
-      pbarrier();
+      wait_stage<LPS, NS - 2>(nstage - 1 - s);
+      wg_barrier();
       MAFAT_PTRACE(8 + s);
       if (s + NS - 1 < nstage) issue(s + NS - 1, slot == 0 ? NS - 1 : slot - 1);
       compute(slot);

@@ -67,36 +67,6 @@ MAFAT_WG_TRACE_DECL(g_wg_ring)
 #endif
 namespace {
 
-typedef __attribute__((address_space(3))) void* lds_ptr_t;
-
-// Wait until at most N of this thread's vector memory operations are
-// outstanding.  (Loads complete in issue order.)
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-  static_assert(N >= 0 && N <= 63, "vmcnt range");
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-
-// Wait until the loads of the oldest outstanding stage have landed, when
-// `rem` later stages (L loads each, at most R of them) are in flight.
-template <int L, int R>
-__device__ __forceinline__ void wait_stage(int rem) {
-  if constexpr (R == 0) {
-    wait_vmcnt<0>();
-  } else {
-    if (rem >= R) {
-      wait_vmcnt<R * L>();
-    } else {
-      wait_stage<L, R - 1>(rem);
-    }
-  }
-}
-
-// Workgroup barrier without a memory fence (the fence of __syncthreads
-// would wait for every outstanding LDS load); the "memory" clobber keeps
-// the compiler from moving LDS reads across it.
-__device__ __forceinline__ void wg_barrier() { asm volatile("s_barrier" ::: "memory"); }
-
 template <int BM, int BN, int WGM, int WGN, int NS, bool POOL>
 __global__ __launch_bounds__(64 * WGM * WGN) void conv_ring_kernel(const StageArgs a) {
   if (__builtin_expect(blockIdx.y != 0, 0)) {  // the second grid row: carried band copies (row reuse)

@@ -54,10 +54,6 @@
 namespace mafat {
 namespace {
 
-// Every LDS operation of this wave done, then the workgroup's barrier (loads
-// into registers stay in flight).
-__device__ __forceinline__ void split_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 // Two floats to the nearest bf16 (ties to even), packed; and its two values.
 __device__ __forceinline__ unsigned near2(float a, float b) {
   typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -288,20 +284,20 @@ __global__ __launch_bounds__(64 * WGM * WGN) void conv_split_kernel(const StageA
     }
 #pragma unroll
   for (int k = 0; k < NI; ++k) commit(G0{}, k, 0, 0);
-  split_barrier();
+  wg_barrier_writes();
   // Step (c, g): fetches the job of (c + 1, g), three steps on, and writes the
   // next step's.
   int aslot = 0, bslot = 0;
   for (int c = 0; c + 1 < nchunk; ++c) {
     fetch(G0{}, c + 1);
     step(G0{}, G1{}, aslot, aslot ^ 1, bslot, true);
-    split_barrier();
+    wg_barrier_writes();
     fetch(G1{}, c + 1);
     step(G1{}, G2{}, aslot, aslot ^ 1, bslot ^ 1, true);
-    split_barrier();
+    wg_barrier_writes();
     fetch(G2{}, c + 1);
     step(G2{}, G0{}, aslot, aslot ^ 1, bslot, true);
-    split_barrier();
+    wg_barrier_writes();
     aslot ^= 1;
     bslot ^= 1;
   }
@@ -319,9 +315,9 @@ __global__ __launch_bounds__(64 * WGM * WGN) void conv_split_kernel(const StageA
     }
   }
   step(G0{}, G1{}, aslot, aslot ^ 1, bslot, true);
-  split_barrier();
+  wg_barrier_writes();
   step(G1{}, G2{}, aslot, aslot ^ 1, bslot ^ 1, true);
-  split_barrier();
+  wg_barrier_writes();
   step(G2{}, G0{}, aslot, aslot ^ 1, bslot, false);
 
   // Epilogue, from registers: folded batch-norm, activation, the fused pool.

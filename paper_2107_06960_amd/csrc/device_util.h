@@ -185,6 +185,38 @@ __device__ __forceinline__ void carried_copies() {
   }
 }
 
+// Helpers of the kernels that load straight into LDS (conv_patch.hip,
+// conv_ring.hip, conv_any.hip) and of conv_split.hip.
+typedef __attribute__((address_space(3))) void* lds_ptr_t;
+
+// Wait until at most N of this thread's vector memory operations are
+// outstanding.  (Loads complete in issue order.)
+template <int N>
+__device__ __forceinline__ void wait_vmcnt() {
+  static_assert(N >= 0 && N <= 63, "vmcnt range");
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+// Wait for the oldest stage when `rem` later ones (L loads each, at most R)
+// are in flight.
+template <int L, int R>
+__device__ __forceinline__ void wait_stage(int rem) {
+  if constexpr (R == 0) {
+    wait_vmcnt<0>();
+  } else {
+    if (rem >= R) {
+      wait_vmcnt<R * L>();
+    } else {
+      wait_stage<L, R - 1>(rem);
+    }
+  }
+}
+// The barrier alone: for slots that LDS DMA fills (wait_vmcnt first) and that
+// are only read, their reads having been waited for by the MFMAs that use them.
+__device__ __forceinline__ void wg_barrier() { asm volatile("s_barrier" ::: "memory"); }
+// After LDS writes of this wave that other waves read: they have to land first
+// (loads into registers stay in flight).
+__device__ __forceinline__ void wg_barrier_writes() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 // Helpers of the patch kernels (conv_patch.hip, conv_split.hip).
 // Byte offset of 16-byte chunk q of 64-byte weight row `row` in a slot region.
 __device__ __forceinline__ int swz(int row, int q) { return row * 64 + ((q ^ ((row >> 1) & 3)) << 4); }
